@@ -23,6 +23,9 @@
 //     the larger row groups use NA = 2, DEPTH = 4.
 //   * Each XCD takes blocks of its vocabulary tiles x row groups (tile_of), so its resident
 //     workgroups share the K-slices of h and W they read through its L2.
+#include <type_traits>
+#include <utility>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -45,11 +48,22 @@ template <int N>
 __device__ __forceinline__ void wait_lgkm() {
   asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory");
 }
-// One 16-byte LDS read, written as an instruction (byte address addr).
+// One 16-byte LDS read, written as an instruction (byte address addr + off, off a constant).
+template <int kOff>
 __device__ __forceinline__ u32x4 lds_read_b128(uint32_t addr) {
+  static_assert(kOff >= 0 && kOff < 65536, "the instruction's offset field");
   u32x4 v;
-  asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr) : "memory");
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(kOff) : "memory");
   return v;
+}
+// f(0), ..., f(N - 1) with compile-time indices.
+template <typename F, int... I>
+__device__ __forceinline__ void for_constants_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void for_constants(F&& f) {
+  for_constants_impl(f, std::make_integer_sequence<int, N>{});
 }
 // Ties a register to the wait before it: no use of v moves above that wait.
 __device__ __forceinline__ void tie(u32x4& v) { asm volatile("" : "+v"(v)); }
@@ -412,16 +426,21 @@ void lm_head_wide_kernel(LmParams p) {
     const int q = (wave * kWCopies + u) * 64 + lane;
     woff[u] = ((q >> 8) * (p.d / kLmK) * kPackTile + 8 * (q & 255)) * 2;
   }
-  auto copy_step = [&](int j, int stage) {
-#pragma unroll
-    for (int u = 0; u < kHCopies; ++u)
+  // copy instruction u of step j (the wave's h copies first, then its W copies)
+  auto copy_one = [&](int j, int stage, int u) {
+    if (u < kHCopies)
       buffer_load_lds16(hrs, (__attribute__((address_space(3))) void*)(sm + stage * kHStage + (wave * kHCopies + u) * 64),
                         hoff[u], j * kLmK * 2);
+    else
+      buffer_load_lds16(wrs,
+                        (__attribute__((address_space(3))) void*)(sm + 2 * kHStage + stage * kWStage +
+                                                                  (wave * kWCopies + u - kHCopies) * 64),
+                        woff[u - kHCopies], j * kPackTile * 2);
+  };
+  constexpr int kCopies = kHCopies + kWCopies;
+  auto copy_step = [&](int j, int stage) {
 #pragma unroll
-    for (int u = 0; u < kWCopies; ++u)
-      buffer_load_lds16(
-          wrs, (__attribute__((address_space(3))) void*)(sm + 2 * kHStage + stage * kWStage + (wave * kWCopies + u) * 64),
-          woff[u], j * kPackTile * 2);
+    for (int u = 0; u < kCopies; ++u) copy_one(j, stage, u);
   };
 
   f32x16 acc[RT][CT];
@@ -446,49 +465,74 @@ void lm_head_wide_kernel(LmParams p) {
   for (int s = 0; s < 4; ++s)
     aaddr[s] = lds0 + (32 * wr * RT + col) * 128 + (((4 * half + s) ^ ((col >> 1) & 7)) << 4);
   const uint32_t baddr = lds0 + 2 * kHStage * 16 + (CT * wc * 256 + lane) * 16;
-  auto lds_read = [](uint32_t addr) { return lds_read_b128(addr); };
-  auto compute = [&](int stage) {
-    u32x4 a[2][RT], b[2][CT];
-    auto frags = [&](int s, int x) {
+  u32x4 fa[2][RT], fb[2][CT];   // fragments of the current MFMA step and of the next one
+  auto frags = [&](auto stage, auto step) {   // of MFMA step `step` of a stage, into set step % 2
+    constexpr int st = decltype(stage)::value, sp = decltype(step)::value;
+    for_constants<RT>([&](auto t) { fa[sp & 1][t] = lds_read_b128<st * kHStage * 16 + t * 4096>(aaddr[sp]); });
+    for_constants<CT>([&](auto c) { fb[sp & 1][c] = lds_read_b128<st * kWStage * 16 + c * 4096 + sp * 1024>(baddr); });
+  };
+  // tie the fragments to the wait, so that no use of them moves above it
+  auto tie_frags = [&](int x) {
 #pragma unroll
-      for (int t = 0; t < RT; ++t) a[x][t] = lds_read(aaddr[s] + stage * kHStage * 16 + t * 4096);
+    for (int t = 0; t < RT; ++t) tie(fa[x][t]);
 #pragma unroll
-      for (int c = 0; c < CT; ++c) b[x][c] = lds_read(baddr + stage * kWStage * 16 + c * 4096 + s * 1024);
-    };
-    frags(0, 0);
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int x = s & 1;
-      if (s < 3) {
-        frags(s + 1, x ^ 1);
-        wait_lgkm<RT + CT>();   // this step's reads done; the next step's stay in flight
-      } else {
-        wait_lgkm<0>();
-      }
-      // tie the fragments to the wait, so that no use of them moves above it
-#pragma unroll
-      for (int t = 0; t < RT; ++t) tie(a[x][t]);
-#pragma unroll
-      for (int c = 0; c < CT; ++c) tie(b[x][c]);
+    for (int c = 0; c < CT; ++c) tie(fb[x][c]);
+  };
+  auto mfma_one = [&](int x, int t, int c) {
+    acc[t][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fa[x][t]), as_bf16x8(fb[x][c]), acc[t][c], 0, 0, 0);
+  };
+
+  // Step j: four MFMA steps from stage j % 2, the fragments of the next one read before the current
+  // one's MFMAs.  Before the last one's MFMAs every wave has read all of the stage and waits for its
+  // own copies of step j + 1 (issued a whole step ago); the barrier then makes that step visible and
+  // frees the stage, so step j + 1's first fragments and, between the MFMAs, the copies of step
+  // j + 2 go out while the last ten MFMAs run.  (With the barrier between two whole steps, both
+  // waves of a SIMD read a step's first fragments with the matrix cores idle: 4612 against 4252 us
+  // at 4608 x 3584 @ 152064, 344 against 322 us at 320 x 4096 @ 128256.)  Scheduling barriers keep
+  // each group of MFMAs between its own wait and the next one; without them the compiler sank the
+  // third group below the fourth's wait (4509 us).
+  auto k_step = [&](auto stage, auto more, auto copy, int j) {
+    constexpr int st = decltype(stage)::value;
+    for_constants<3>([&](auto s) {
+      frags(stage, std::integral_constant<int, s + 1>{});
+      wait_lgkm<RT + CT>();   // this step's reads done; the next step's stay in flight
+      tie_frags(s & 1);
 #pragma unroll
       for (int t = 0; t < RT; ++t)
 #pragma unroll
-        for (int c = 0; c < CT; ++c)
-          acc[t][c] =
-              __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a[x][t]), as_bf16x8(b[x][c]), acc[t][c], 0, 0, 0);
+        for (int c = 0; c < CT; ++c) mfma_one(s & 1, t, c);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    wait_lgkm<0>();
+    tie_frags(1);
+    if constexpr (decltype(more)::value) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      frags(std::integral_constant<int, st ^ 1>{}, std::integral_constant<int, 0>{});
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < RT * CT || u < kCopies; ++u) {
+      if (u < RT * CT) mfma_one(1, u / CT, u % CT);
+      __builtin_amdgcn_sched_barrier(0);
+      if (decltype(copy)::value && u < kCopies) copy_one(j + 2, st, u);
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
-
-  // step j: wait for this wave's copies of step j, then the barrier makes every wave's copies
-  // visible and tells that all have finished step j - 1, whose stage step j + 1 now fills while
-  // step j is computed
+  using Stage0 = std::integral_constant<int, 0>;
+  using Stage1 = std::integral_constant<int, 1>;
   copy_step(0, 0);
-  for (int j = 0; j < nsteps; ++j) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (j + 1 < nsteps) copy_step(j + 1, (j + 1) & 1);
-    compute(j & 1);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  copy_step(1, 1);
+  frags(Stage0{}, Stage0{});
+  int j = 0;   // an even number of steps, at least four (d is a multiple of 256)
+  for (; j + 2 < nsteps; j += 2) {
+    k_step(Stage0{}, std::true_type{}, std::true_type{}, j);
+    k_step(Stage1{}, std::true_type{}, std::true_type{}, j + 1);
   }
+  k_step(Stage0{}, std::true_type{}, std::false_type{}, j);
+  k_step(Stage1{}, std::false_type{}, std::false_type{}, j + 1);
   __syncthreads();   // the epilogue's transposes reuse h stage 0
 
   // ---- epilogue (accumulator value i of lane l in tile (t, c): row 32 (wr RT + t) + 8 (i / 4)
