@@ -108,6 +108,132 @@ __device__ __forceinline__ void tile_of(int bid, int ntiles, int groups, int& nt
   mg = g;
 }
 
+// A workgroup's accumulators to memory: fp32 logits (or K-split partials) at `out` and / or bf16
+// outputs at y (+ residual), both with row stride V, from row m0 on.  One pointer per lane and
+// column tile, to which each store adds its accumulator's row offset (uniform); a group of whole
+// 32-row tiles takes no row checks.  fp32 values are written once and read by a later kernel:
+// non-temporal stores keep them from evicting the h and W lines the other workgroups still read
+// through L2 (measured at 320 x 4096 @ 128256: 469 against 480 us; at 4608 x 3584 @ 152064: 5332
+// against 5684 us).
+template <int RT, int CT, int WR, int WC>
+__device__ __forceinline__ void store_epilogue(const f32x16 (&acc)[RT][CT], float* out, uint16_t* y, const uint16_t* res,
+                                               int V, int m0, int n0, int rows, int wr, int wc, int lane) {
+  const int col = lane & 31, half = lane >> 5;
+  const bool full = rows == 32 * WR * RT;
+  const int r0 = 32 * wr * RT + 4 * half;   // row of accumulator (t, i): r0 + 32 t + 8 (i / 4) + i % 4
+#pragma unroll
+  for (int c = 0; c < CT; ++c) {
+    const int v = n0 + 32 * (CT * wc + c) + col;
+    if (v >= V) continue;
+    if (out) {
+      float* at = out + (int64_t)(m0 + r0) * V + v;
+#pragma unroll
+      for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int dr = 32 * t + 8 * (i >> 2) + (i & 3);
+          if (full || r0 + dr < rows) __builtin_nontemporal_store(acc[t][c][i], at + (int64_t)dr * V);
+        }
+    }
+    if (y) {
+#pragma unroll
+      for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int r = r0 + 32 * t + 8 * (i >> 2) + (i & 3);
+          if (r < rows) {
+            const int64_t at = (int64_t)(m0 + r) * V + v;
+            y[at] = bf16_rne(res ? acc[t][c][i] + bf16_float(res[at]) : acc[t][c][i]);
+          }
+        }
+    }
+  }
+}
+
+// Row statistics of a workgroup's accumulators over its 128-column tiles, and the gathered logits
+// (the epilogue of both kernels).  Waves form a WR x WC grid of RT x CT accumulator tiles; tile
+// (t, c) of lane l, value i: row 32 (wr RT + t) + 8 (i / 4) + 4 (l / 32) + i % 4, column
+// n0 + 32 (CT wc + c) + l % 32.  Each wave transposes one 32 x 32 tile at a time through its part of
+// `scratch` (32 x 36 floats per wave); lane l then reduces 16 columns of row l % 32 (columns
+// 16 (l / 32) ..), the two halves of a row combine in one cross-half lane swap, then the wave's CT
+// tiles in order, and the waves of a 128-column tile in order at the end.  (Lanes 0 .. 31 reducing
+// whole rows left half the wave idle in the exponentials: 8 us more per workgroup of 320 rows.)
+// Adds of two halves commute, so both halves of the wave hold the same row statistics.
+template <int RT, int CT, int WR, int WC>
+__device__ __forceinline__ void row_stats_epilogue(float* stats, float* gout, float scale, int V, int ntiles,
+                                                   const f32x16 (&acc)[RT][CT], const int (&gcol)[RT],
+                                                   int nt, int m0, int n0, int rows, int wr, int wc, int lane,
+                                                   float* scratch, float (&sm_m)[WC][32 * WR * RT],
+                                                   float (&sm_z)[WC][32 * WR * RT]) {
+  constexpr int kStatTiles = 32 * WC * CT / kLmCols;   // 128-column statistics tiles of the workgroup
+  constexpr int kTS = 36;   // floats per transposed row (16-byte aligned, padded)
+  const int col = lane & 31, half = lane >> 5;
+  float* tile = scratch + (wr * WC + wc) * 32 * kTS;
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    float wm = -INFINITY, wz = 0.f;
+    const int grow = 32 * (wr * RT + t) + col;   // this lane's row
+    const int gc = gcol[t];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+      // x c rounded once, then x c - max: no contraction into one fused operation
+#pragma clang fp contract(off)
+      const int cb = n0 + 32 * (CT * wc + c);   // the tile's first column
+      const bool live = cb + col < V;
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        tile[(8 * (i >> 2) + 4 * half + (i & 3)) * kTS + col] = live ? acc[t][c][i] : -INFINITY;
+      const float* mine = tile + col * kTS + 16 * half;   // 16 columns of this lane's row
+      f32x4 x[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) x[q] = *reinterpret_cast<const f32x4*>(mine + 4 * q) * scale;
+      const int gl = gc - cb - 16 * half;
+      if (gl >= 0 && gl < 16 && gc < V) gout[m0 + grow] = mine[gl];
+      float mx = -INFINITY;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) mx = fmaxf(fmaxf(mx, fmaxf(x[q][0], x[q][1])), fmaxf(x[q][2], x[q][3]));
+      const auto rm = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+      mx = fmaxf(__uint_as_float(rm[0]), __uint_as_float(rm[1]));
+      float e = 0.f;
+      if (mx != -INFINITY) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) e += fast_exp2(x[q][u] - mx);
+      }
+      const auto re = __builtin_amdgcn_permlane32_swap(__float_as_uint(e), __float_as_uint(e), false, false);
+      e = __uint_as_float(re[0]) + __uint_as_float(re[1]);
+      if (c == 0) {
+        wm = mx;
+        wz = e;
+      } else {
+        const float M = fmaxf(wm, mx);
+        wz = (wm != -INFINITY ? wz * fast_exp2(wm - M) : 0.f) + (mx != -INFINITY ? e * fast_exp2(mx - M) : 0.f);
+        wm = M;
+      }
+    }
+    if (half == 0) {
+      sm_m[wc][grow] = wm;
+      sm_z[wc][grow] = wz;
+    }
+  }
+  __syncthreads();
+  constexpr int kWavesPerStat = WC / kStatTiles;   // waves of a row within one statistics tile
+  for (int q = threadIdx.x; q < rows * kStatTiles; q += 64 * WR * WC) {
+    const int r = q % rows, st = q / rows, w0 = st * kWavesPerStat;
+    const int stile = nt * kStatTiles + st;
+    if (stile >= ntiles) continue;
+    float M = sm_m[w0][r];
+#pragma unroll
+    for (int w = 1; w < kWavesPerStat; ++w) M = fmaxf(M, sm_m[w0 + w][r]);
+    float Z = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWavesPerStat; ++w)
+      if (sm_m[w0 + w][r] != -INFINITY) Z += sm_z[w0 + w][r] * fast_exp2(sm_m[w0 + w][r] - M);
+    *reinterpret_cast<f32x2*>(stats + ((int64_t)(m0 + r) * ntiles + stile) * 2) = f32x2{M, Z};
+  }
+}
+
 }  // namespace
 
 // Waves form a WR x WC grid over the workgroup's (32 * WR * RT) rows x (32 * WC * CT) columns:
@@ -122,7 +248,6 @@ void lm_head_kernel(LmParams p) {
   static_assert(DEPTH >= NA + 2 && DEPTH % NA == 0 && DEPTH % 2 == 0, "pipeline shape");
   constexpr int WC = 4 / WR;
   constexpr int kCols = 32 * WC * CT;           // columns of the workgroup
-  constexpr int kStatTiles = kCols / kLmCols;   // its 128-column statistics tiles
   static_assert(WR * WC == 4 && (kCols == 128 || kCols == 256), "wave grid");
   constexpr int NRT = WR * RT;   // row tiles of the workgroup
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
@@ -238,124 +363,23 @@ void lm_head_kernel(LmParams p) {
     }
   }
 
-  // ---- epilogue: logits (or partials, or bf16 outputs), and each row's statistics over each
-  // of this workgroup's 128-column statistics tiles.  Accumulator value i of lane l in tile (t, c): row
-  // 32 (wr RT + t) + 8 (i / 4) + 4 (l / 32) + i % 4, column 32 (CT wc + c) + l % 32.
-  auto out_row = [&](int t, int i) { return 32 * (wr * RT + t) + 8 * (i >> 2) + 4 * half + (i & 3); };
-  auto out_col = [&](int c) { return n0 + 32 * (CT * wc + c) + col; };
-  // Logits (or K-split partials) are written once and read by a later kernel: non-temporal
-  // stores keep them from evicting the h and W lines the other workgroups still read through L2
-  // (measured at 320 x 4096 @ 128256: 469 against 480 us; at 4608 x 3584 @ 152064: 5332 against
-  // 5684 us).
-  // the gather columns of the rows lanes below 32 reduce in the statistics (loaded first: their
-  // latency passes under the logits stores)
+  // ---- epilogue: logits (or partials, or bf16 outputs), and each row's statistics over each of
+  // this workgroup's 128-column statistics tiles.  The gather columns of the rows each lane reduces
+  // in the statistics are loaded first: their latency passes under the stores.
   int gcol[RT];
 #pragma unroll
   for (int t = 0; t < RT; ++t) {
-    const int grow = 32 * (wr * RT + t) + lane;
-    gcol[t] = p.gout && p.stats && lane < 32 && grow < rows ? p.gcols[m0 + grow] : -1;
+    const int grow = 32 * (wr * RT + t) + col;
+    gcol[t] = p.gout && p.stats && grow < rows ? p.gcols[m0 + grow] : -1;
   }
-  if (p.logits) {
-    float* out = p.logits + (int64_t)ks * p.M * p.V;
-#pragma unroll
-    for (int c = 0; c < CT; ++c) {
-      const int v = out_col(c);
-      if (v >= p.V) continue;
-#pragma unroll
-      for (int t = 0; t < RT; ++t)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int r = out_row(t, i);
-          if (r < rows) __builtin_nontemporal_store(acc[t][c][i], out + (int64_t)(m0 + r) * p.V + v);
-        }
-    }
-  }
-  if (p.y) {
-    const uint16_t* res = reinterpret_cast<const uint16_t*>(p.res);
-    uint16_t* y = reinterpret_cast<uint16_t*>(p.y);
-#pragma unroll
-    for (int c = 0; c < CT; ++c) {
-      const int v = out_col(c);
-      if (v >= p.V) continue;
-#pragma unroll
-      for (int t = 0; t < RT; ++t)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int r = out_row(t, i);
-          if (r < rows) {
-            const int64_t at = (int64_t)(m0 + r) * p.V + v;
-            y[at] = bf16_rne(res ? acc[t][c][i] + bf16_float(res[at]) : acc[t][c][i]);
-          }
-        }
-    }
-  }
+  store_epilogue<RT, CT, WR, WC>(acc, p.logits ? p.logits + (int64_t)ks * p.M * p.V : nullptr,
+                                 reinterpret_cast<uint16_t*>(p.y), reinterpret_cast<const uint16_t*>(p.res), p.V, m0, n0,
+                                 rows, wr, wc, lane);
   if (!p.stats) return;
-  // Row statistics: each wave transposes one 32x32 tile at a time through its part of the (now
-  // free) h stages; lane r < 32 reduces row r over the tile's 32 columns, then over the wave's
-  // CT tiles in order; the waves of a row and 128-column statistics tile are combined in order
-  // at the end.
+  // through the (now free) h stages
   __shared__ float sm_m[WC][32 * NRT], sm_z[WC][32 * NRT];
-  constexpr int kTS = 36;   // floats per transposed row (16-byte aligned, padded)
-  float* tile = reinterpret_cast<float*>(&sm_a[0][0]) + wave * 32 * kTS;
-#pragma unroll
-  for (int t = 0; t < RT; ++t) {
-    float wm = -INFINITY, wz = 0.f;
-    const int grow = 32 * (wr * RT + t) + lane;
-    const int gc = gcol[t];
-#pragma unroll
-    for (int c = 0; c < CT; ++c) {
-      const bool live = out_col(c) < p.V;
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-        tile[(8 * (i >> 2) + 4 * half + (i & 3)) * kTS + col] = live ? acc[t][c][i] : -INFINITY;
-      if (lane < 32) {
-        // x c rounded once, then x c - max: no contraction into one fused operation
-#pragma clang fp contract(off)
-        f32x4 x[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) x[q] = *reinterpret_cast<const f32x4*>(tile + lane * kTS + 4 * q) * p.c;
-        const int cb = out_col(c) - col;   // the tile's first column
-        if (gc >= cb && gc < cb + 32 && gc < p.V) p.gout[m0 + grow] = tile[lane * kTS + (gc - cb)];
-        float mx = -INFINITY;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) mx = fmaxf(fmaxf(mx, fmaxf(x[q][0], x[q][1])), fmaxf(x[q][2], x[q][3]));
-        float e = 0.f;
-        if (mx != -INFINITY) {
-#pragma unroll
-          for (int q = 0; q < 8; ++q)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) e += fast_exp2(x[q][u] - mx);
-        }
-        if (c == 0) {
-          wm = mx;
-          wz = e;
-        } else {
-          const float M = fmaxf(wm, mx);
-          wz = (wm != -INFINITY ? wz * fast_exp2(wm - M) : 0.f) + (mx != -INFINITY ? e * fast_exp2(mx - M) : 0.f);
-          wm = M;
-        }
-      }
-    }
-    if (lane < 32) {
-      sm_m[wc][32 * (wr * RT + t) + lane] = wm;
-      sm_z[wc][32 * (wr * RT + t) + lane] = wz;
-    }
-  }
-  __syncthreads();
-  constexpr int kWavesPerStat = WC / kStatTiles;   // waves of a row within one statistics tile
-  for (int q = threadIdx.x; q < rows * kStatTiles; q += 256) {
-    const int r = q % rows, st = q / rows, w0 = st * kWavesPerStat;
-    const int tile = nt * kStatTiles + st;
-    if (tile >= p.ntiles) continue;
-    float M = sm_m[w0][r];
-#pragma unroll
-    for (int w = 1; w < kWavesPerStat; ++w) M = fmaxf(M, sm_m[w0 + w][r]);
-    float Z = 0.f;
-#pragma unroll
-    for (int w = 0; w < kWavesPerStat; ++w)
-      if (sm_m[w0 + w][r] != -INFINITY) Z += sm_z[w0 + w][r] * fast_exp2(sm_m[w0 + w][r] - M);
-    *reinterpret_cast<f32x2*>(p.stats + ((int64_t)(m0 + r) * p.ntiles + tile) * 2) = f32x2{M, Z};
-  }
+  row_stats_epilogue<RT, CT, WR, WC>(p.stats, p.gout, p.c, p.V, p.ntiles, acc, gcol, nt, m0, n0, rows, wr, wc, lane,
+                                     reinterpret_cast<float*>(&sm_a[0][0]), sm_m, sm_z);
 }
 
 // More than 160 rows of a wide projection (an LM head's vocabulary): one workgroup of eight waves
@@ -376,8 +400,7 @@ void lm_head_wide_kernel(LmParams p) {
   constexpr int NRT = WR * RT;        // row tiles of the workgroup
   constexpr int kRows = 32 * NRT;     // rows of the group
   constexpr int kCols = 32 * WC * CT; // columns of the workgroup
-  constexpr int kStatTiles = kCols / kLmCols;
-  static_assert(kCols == 256 && WC % kStatTiles == 0, "two 128-column statistics tiles, whole waves each");
+  static_assert(kCols == 256 && WC % 2 == 0, "two 128-column statistics tiles, whole waves each");
   // the wave index wave-uniform (scalar), so the copies' LDS destinations are scalar sums
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
@@ -535,117 +558,19 @@ void lm_head_wide_kernel(LmParams p) {
   k_step(Stage1{}, std::false_type{}, std::false_type{}, j + 1);
   __syncthreads();   // the epilogue's transposes reuse h stage 0
 
-  // ---- epilogue (accumulator value i of lane l in tile (t, c): row 32 (wr RT + t) + 8 (i / 4)
-  // + 4 (l / 32) + i % 4, column 32 (CT wc + c) + l % 32)
-  auto out_row = [&](int t, int i) { return 32 * (wr * RT + t) + 8 * (i >> 2) + 4 * half + (i & 3); };
-  auto out_col = [&](int c) { return n0 + 32 * (CT * wc + c) + col; };
-  // the gather columns of the rows lanes below 32 reduce in the statistics (loaded first: their
-  // latency passes under the logits stores)
+  // ---- epilogue (the gather columns first, as above)
   int gcol[RT];
 #pragma unroll
   for (int t = 0; t < RT; ++t) {
-    const int grow = 32 * (wr * RT + t) + lane;
-    gcol[t] = p.gout && p.stats && lane < 32 && grow < rows ? p.gcols[m0 + grow] : -1;
+    const int grow = 32 * (wr * RT + t) + col;
+    gcol[t] = p.gout && p.stats && grow < rows ? p.gcols[m0 + grow] : -1;
   }
-  if (p.logits) {
-#pragma unroll
-    for (int c = 0; c < CT; ++c) {
-      const int v = out_col(c);
-      if (v >= p.V) continue;
-#pragma unroll
-      for (int t = 0; t < RT; ++t)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int r = out_row(t, i);
-          if (r < rows) __builtin_nontemporal_store(acc[t][c][i], p.logits + (int64_t)(m0 + r) * p.V + v);
-        }
-    }
-  }
-  if (p.y) {
-    const uint16_t* res = reinterpret_cast<const uint16_t*>(p.res);
-    uint16_t* y = reinterpret_cast<uint16_t*>(p.y);
-#pragma unroll
-    for (int c = 0; c < CT; ++c) {
-      const int v = out_col(c);
-      if (v >= p.V) continue;
-#pragma unroll
-      for (int t = 0; t < RT; ++t)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int r = out_row(t, i);
-          if (r < rows) {
-            const int64_t at = (int64_t)(m0 + r) * p.V + v;
-            y[at] = bf16_rne(res ? acc[t][c][i] + bf16_float(res[at]) : acc[t][c][i]);
-          }
-        }
-    }
-  }
+  store_epilogue<RT, CT, WR, WC>(acc, p.logits, reinterpret_cast<uint16_t*>(p.y),
+                                 reinterpret_cast<const uint16_t*>(p.res), p.V, m0, n0, rows, wr, wc, lane);
   if (!p.stats) return;
-  // Row statistics: each wave transposes one 32x32 tile at a time through its part of the (now
-  // free) h stages; lane r < 32 reduces row r over the tile's 32 columns, then over the wave's CT
-  // tiles in order; the two waves of a row and 128-column statistics tile combine in order.
-  __shared__ float sm_m[WC][kRows], sm_z[WC][kRows];
-  constexpr int kTS = 36;   // floats per transposed row (16-byte aligned, padded)
-  float* tile = reinterpret_cast<float*>(&sm[0]) + wave * 32 * kTS;
-#pragma unroll
-  for (int t = 0; t < RT; ++t) {
-    float wm = -INFINITY, wz = 0.f;
-    const int grow = 32 * (wr * RT + t) + lane;
-    const int gc = gcol[t];
-#pragma unroll
-    for (int c = 0; c < CT; ++c) {
-      const bool live = out_col(c) < p.V;
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-        tile[(8 * (i >> 2) + 4 * half + (i & 3)) * kTS + col] = live ? acc[t][c][i] : -INFINITY;
-      if (lane < 32) {
-        // x c rounded once, then x c - max: no contraction into one fused operation
-#pragma clang fp contract(off)
-        f32x4 x[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) x[q] = *reinterpret_cast<const f32x4*>(tile + lane * kTS + 4 * q) * p.c;
-        const int cb = out_col(c) - col;   // the tile's first column
-        if (gc >= cb && gc < cb + 32 && gc < p.V) p.gout[m0 + grow] = tile[lane * kTS + (gc - cb)];
-        float mx = -INFINITY;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) mx = fmaxf(fmaxf(mx, fmaxf(x[q][0], x[q][1])), fmaxf(x[q][2], x[q][3]));
-        float e = 0.f;
-        if (mx != -INFINITY) {
-#pragma unroll
-          for (int q = 0; q < 8; ++q)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) e += fast_exp2(x[q][u] - mx);
-        }
-        if (c == 0) {
-          wm = mx;
-          wz = e;
-        } else {
-          const float M = fmaxf(wm, mx);
-          wz = (wm != -INFINITY ? wz * fast_exp2(wm - M) : 0.f) + (mx != -INFINITY ? e * fast_exp2(mx - M) : 0.f);
-          wm = M;
-        }
-      }
-    }
-    if (lane < 32) {
-      sm_m[wc][32 * (wr * RT + t) + lane] = wm;
-      sm_z[wc][32 * (wr * RT + t) + lane] = wz;
-    }
-  }
-  __syncthreads();
-  constexpr int kWavesPerStat = WC / kStatTiles;
-  for (int q = threadIdx.x; q < rows * kStatTiles; q += 64 * kWaves) {
-    const int r = q % rows, st = q / rows, w0 = st * kWavesPerStat;
-    const int stile = nt * kStatTiles + st;
-    if (stile >= p.ntiles) continue;
-    float M = sm_m[w0][r];
-#pragma unroll
-    for (int w = 1; w < kWavesPerStat; ++w) M = fmaxf(M, sm_m[w0 + w][r]);
-    float Z = 0.f;
-#pragma unroll
-    for (int w = 0; w < kWavesPerStat; ++w)
-      if (sm_m[w0 + w][r] != -INFINITY) Z += sm_z[w0 + w][r] * fast_exp2(sm_m[w0 + w][r] - M);
-    *reinterpret_cast<f32x2*>(p.stats + ((int64_t)(m0 + r) * p.ntiles + stile) * 2) = f32x2{M, Z};
-  }
+  __shared__ float sm_m[WC][kRows], sm_z[WC][kRows];   // the transposes: the (now free) h stage 0
+  row_stats_epilogue<RT, CT, WR, WC>(p.stats, p.gout, p.c, p.V, p.ntiles, acc, gcol, nt, m0, n0, rows, wr, wc, lane, reinterpret_cast<float*>(&sm[0]),
+                                     sm_m, sm_z);
 }
 
 template <int RT, int CT, int WR, int NA, int DEPTH, int WPE>
