@@ -512,6 +512,7 @@ int spexis_linear(const void* x, const void* weight, const void* residual, int32
   p.M = rows;
   p.N = out_features;
   p.S = S;
+  p.vec4 = out_features % 4 == 0 && ((uintptr_t)y | (uintptr_t)residual) % 8 == 0;
   return hip_result(spexis::launch_linear(p, (hipStream_t)stream), "spexis_linear");
 }
 
@@ -565,9 +566,11 @@ int spexis_linear_split(const void* x, const void* weight, int32_t rows, int32_t
   p.S = S;
   p.nout = num_outputs;
   p.off[0] = 0;
+  p.vec4 = 1;
   for (int i = 0; i < num_outputs; ++i) {
     p.off[i + 1] = p.off[i] + out_features[i];
     p.ys[i] = outputs[i];
+    p.vec4 &= (uintptr_t)outputs[i] % 8 == 0;   // every width is a multiple of 4
   }
   for (int i = num_outputs + 1; i <= spexis::kLinearMaxOutputs; ++i) p.off[i] = (int)N;
   return hip_result(spexis::launch_linear(p, (hipStream_t)stream), "spexis_linear_split");

@@ -95,6 +95,7 @@ struct LinearParams {
   int nout;                          // 0: y alone; else outputs 0 .. nout-1 take columns
   int off[kLinearMaxOutputs + 1];    // off[i] .. off[i+1]-1 (multiples of 4, off[nout] = N)
   void* ys[kLinearMaxOutputs];       // bf16 [M][off[i+1] - off[i]]
+  int vec4;                          // N % 4 == 0 and every output and the residual 8-byte aligned
 };
 
 struct LookaheadParams {

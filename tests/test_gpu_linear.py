@@ -161,3 +161,31 @@ def test_pack_weight_layout(N, K):
     w, wb = bf16_pair((N, K), N + K, 1.0)
     got = sx.spexis_pack_weight(w.cuda()).view(torch.int16).cpu().numpy().view(np.uint16)
     np.testing.assert_array_equal(got, packed_reference(wb))
+
+
+@pytest.mark.parametrize("rows,n_out,n_in,res", [
+    (32, 33, 256, True),        # one row tile, a second column tile of one column, waves without a K-step
+    (33, 64, 8192, False),      # two groups of 32 rows, the longest K of the one-launch kernel
+    (65, 2752, 256, True),      # groups of 64 rows, the second of one row
+    (64, 8224, 512, False),     # 64 x 32 tiles' last full launch is 256 column tiles: 257 take 64 x 64
+    (130, 4101, 256, True),     # 64 x 64 tiles, columns not a multiple of 4, an odd count of column tiles
+    (3, 40, 8448, True),        # a longer K: split over workgroups, reduced in a second launch
+])
+def test_linear_tile_edges(rows, n_out, n_in, res):
+    check(rows, n_out, n_in, res, rows * 7 + n_out)
+
+
+@pytest.mark.parametrize("n_out", [40, 42])
+def test_linear_outputs_at_any_alignment(n_out):
+    # y and the residual two bytes past an 8-byte boundary (and, at 42, rows of 84 bytes): the same
+    # values as into aligned tensors
+    rows, n_in = 5, 512
+    x, _ = bf16_pair((rows, n_in), 3, 1.0)
+    w, _ = bf16_pair((n_out, n_in), 4, 0.03)
+    r, _ = bf16_pair((rows, n_out), 5, 1.0)
+    want, _ = run(x, w, r)
+    off = [torch.zeros(rows * n_out + 1, dtype=torch.bfloat16, device="cuda")[1:].view(rows, n_out) for _ in range(2)]
+    off[0].copy_(r)
+    ws = torch.empty(max(sx.spexis_linear_workspace_size(rows, n_out, n_in), 1), dtype=torch.uint8, device="cuda")
+    sx.spexis_linear(x.cuda(), sx.spexis_pack_weight(w.cuda()), off[1], residual=off[0], workspace=ws)
+    assert np.array_equal(off[1].float().cpu().double().numpy(), want)
