@@ -113,6 +113,16 @@ __device__ __forceinline__ void advance(const AttnParams& p, Cursor& c) {
 // Share geometry of a head's tile stream: shares pair up, shares 2j and 2j+1 covering tiles
 // [2jP, 2(j+1)P), the first (the wave on an even XCD) P + dlt of them and the second P - dlt.
 // dlt = 0 gives equal shares of P.
+// P of a head's `total` tiles: an even split over its shares, but at least kAttnMinTilesPerWave tiles
+// each, and more when a head has many (total / 64, up to kAttnMinTilesLong): a share's start and its
+// partial, written and merged, cost about as much as those tiles (the call at one sequence of 16384
+// keys and 8 KV heads, 512 tiles a head: 25.8 us with shares of 6, 27.0 of 5, 30.3 of 4, 25.9 of 8;
+// at 128 tiles 17.1 us with shares of 2, 17.5 of 4, 18.5 of 6).
+__device__ __forceinline__ int share_tiles(const AttnParams& p, int total) {
+  const int least = p.tiles_per_wave > 0 ? p.tiles_per_wave
+                                         : clampi(total / 64, kAttnMinTilesPerWave, kAttnMinTilesLong);
+  return max(least, (total + p.nshares - 1) / p.nshares);
+}
 __device__ __forceinline__ int share_delta(int P, int skew) { return (int)(((int64_t)P * skew) >> 10); }
 __device__ __forceinline__ int64_t share_first(int s, int P, int dlt) {
   return (int64_t)(s >> 1) * 2 * P + (s & 1) * (P + dlt);
@@ -166,8 +176,7 @@ void verify_attn_kernel(AttnParams p) {
     const SeqGeo gl = lane < p.num_seqs ? seq_geo(p, p.qsl, p.seq_lens, lane) : SeqGeo{0, 0, 0, 0};
     const int incl = wave_incl_scan_i32(gl.nt, lane);
     total = __builtin_amdgcn_readlane(incl, kWave - 1);   // < 2^31 (host)
-    const int even = (total + p.nshares - 1) / p.nshares;
-    const int P = max(p.tiles_per_wave > 0 ? p.tiles_per_wave : kAttnMinTilesPerWave, even);
+    const int P = share_tiles(p, total);
     if (share_first(share, P, share_delta(P, p.skew)) >= total) return no_share();
     const int g0 = (int)share_first(share, P, share_delta(P, p.skew));
     const uint64_t hit = __builtin_amdgcn_ballot_w64(incl > g0);
@@ -184,8 +193,7 @@ void verify_attn_kernel(AttnParams p) {
     for (int base = 0; base < p.num_seqs; base += kWave)
       if (base + lane < p.num_seqs) per_lane += seq_geo(p, p.qsl, p.seq_lens, base + lane).nt;
     total = __builtin_amdgcn_readfirstlane(wave_sum_i32(per_lane));   // < 2^31 (host)
-    const int even = (total + p.nshares - 1) / p.nshares;
-    const int P = max(p.tiles_per_wave > 0 ? p.tiles_per_wave : kAttnMinTilesPerWave, even);
+    const int P = share_tiles(p, total);
     if (share_first(share, P, share_delta(P, p.skew)) >= total) return no_share();
     const int g0 = (int)share_first(share, P, share_delta(P, p.skew));
     // the sequence holding tile g0, and the stream index of its first tile
@@ -212,8 +220,7 @@ void verify_attn_kernel(AttnParams p) {
     start.S = g.S;
     start.t = g0 - f0;
   }
-  const int P = max(p.tiles_per_wave > 0 ? p.tiles_per_wave : kAttnMinTilesPerWave,
-                    (total + p.nshares - 1) / p.nshares);
+  const int P = share_tiles(p, total);
   const int dlt = share_delta(P, p.skew);
   const int g0 = (int)share_first(share, P, dlt);
   const int cnt = min(share_size(share, P, dlt), total - g0);
@@ -669,11 +676,104 @@ __global__ __launch_bounds__(512) void attn_merge_kernel(AttnParams p) {
   }
 }
 
+// The same for few, long items, each cut into many shares (a single sequence: 128): one workgroup per
+// (item, kMergeRows of its rows), whose thread groups take every NG-th contributor, eight at a time with
+// all their loads in flight, and whose groups then combine through LDS in order.  attn_merge_kernel's
+// walk, four contributors a round trip, took 39.8 us for 128 contributors of 20 rows (the whole call
+// 60.7 us; 30.3 with this kernel).  The item's shares
+// follow from the sequence lengths, as in the main kernel, so a workgroup needs no header.
+constexpr int kMergeRows = 4, kMergeWideShares = 16;
+template <int D>
+__global__ __launch_bounds__(512) void attn_merge_wide_kernel(AttnParams p, int row_groups) {
+  constexpr int U = 8, kUnits = kMergeRows * D / U, NG = 512 / kUnits, kBatch = 8;
+  const int lane = threadIdx.x & 63;
+  const int item = blockIdx.x / row_groups, rg = blockIdx.x % row_groups;
+  const int b = item / p.hkv, h = item % p.hkv;
+  int before = 0, all = 0;
+  for (int x = lane; x < p.num_seqs; x += kWave) {
+    const int nt = seq_geo(p, p.qsl, p.seq_lens, x).nt;
+    all += nt;
+    before += x < b ? nt : 0;
+  }
+  const SeqGeo g = seq_geo(p, p.qsl, p.seq_lens, b);
+  const int total = wave_sum_i32(all), f = wave_sum_i32(before);   // < 2^31 (host)
+  const int R = p.group * g.n;
+  if (g.nt == 0 || rg * kMergeRows >= R) return;
+  const int P = share_tiles(p, total);
+  const int dlt = share_delta(P, p.skew);
+  const int s0 = share_of(f, P, dlt);
+  const int C = min(share_of(f + g.nt - 1, P, dlt), p.nshares - 1) - s0 + 1;
+  if (C <= 1) return;   // the main kernel wrote this item whole
+  const int64_t slot_f = attn_slot_floats(p.rmax, D), mo = (int64_t)p.rmax * D, lo = mo + p.rmax;
+  auto slot = [&](int c) -> const float* {
+    return p.ws + ((int64_t)((s0 + c) * p.hkv + h) * 2 + (c == 0 ? 1 : 0)) * slot_f;
+  };
+  const int unit = threadIdx.x % kUnits, cg = threadIdx.x / kUnits;
+  const int r = rg * kMergeRows + unit / (D / U), rl = min(r, R - 1), d = (unit % (D / U)) * U;
+  float M = kNegBig, den = 0.f;
+  f32x4 o0 = {0.f, 0.f, 0.f, 0.f}, o1 = o0;
+  auto add = [&](float mc, float lc, f32x4 a0, f32x4 a1) {
+    const float mn = fmaxf(M, mc), x = fast_exp2(M - mn), e = fast_exp2(mc - mn);
+    den = den * x + lc * e;
+    o0 = o0 * x + a0 * e;
+    o1 = o1 * x + a1 * e;
+    M = mn;
+  };
+  for (int c0 = cg; c0 < C; c0 += NG * kBatch) {
+    float mv[kBatch], lv[kBatch];
+    f32x4 a0[kBatch], a1[kBatch];
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) {
+      const float* sp = slot(min(c0 + k * NG, C - 1));
+      mv[k] = sp[mo + rl];
+      lv[k] = sp[lo + rl];
+      a0[k] = *reinterpret_cast<const f32x4*>(sp + (int64_t)rl * D + d);
+      a1[k] = *reinterpret_cast<const f32x4*>(sp + (int64_t)rl * D + d + 4);
+    }
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k)
+      if (c0 + k * NG < C) add(mv[k], lv[k], a0[k], a1[k]);
+  }
+  __shared__ float sm[NG][kUnits][2 + U];
+  if (cg > 0) {
+    float* e = sm[cg][unit];
+    e[0] = M;
+    e[1] = den;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      e[2 + i] = o0[i];
+      e[6 + i] = o1[i];
+    }
+  }
+  __syncthreads();
+  if (cg > 0 || r >= R) return;
+#pragma unroll 1
+  for (int x = 1; x < NG; ++x) {
+    const float* e = sm[x][unit];
+    if (x < C) add(e[0], e[1], f32x4{e[2], e[3], e[4], e[5]}, f32x4{e[6], e[7], e[8], e[9]});
+  }
+  const float inv = 1.0f / den;
+  const int j = r / p.group, gq = r % p.group;
+  uint16_t* orow = reinterpret_cast<uint16_t*>(p.out) + ((int64_t)(g.q0 + j) * p.hq + h * p.group + gq) * D + d;
+  const u32x4 w = {pack_bf16x2(o0[0] * inv, o0[1] * inv), pack_bf16x2(o0[2] * inv, o0[3] * inv),
+                   pack_bf16x2(o1[0] * inv, o1[1] * inv), pack_bf16x2(o1[2] * inv, o1[3] * inv)};
+  __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(orow));
+}
+
 template <int D, int BS, int NT>
 static hipError_t launch_attn_t(const AttnParams& p, hipStream_t s) {
   hipLaunchKernelGGL((verify_attn_kernel<D, BS, NT>), dim3((unsigned)(p.nwaves / 4)), dim3(256), 0, s, p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  // Few, long items: at least kMergeWideShares shares per sequence (the call, wide merge against
+  // attn_merge_kernel: 30.3 against 60.7 us at one sequence of 16384 keys, 25.7 against 30.8 at 4 of
+  // 1000-4096, 30.2 against 32.0 at 8 of them, where there are 16 shares a sequence; 45.4 against 43.0
+  // at 16 of them).
+  if (p.nshares >= kMergeWideShares * p.num_seqs) {
+    const int rg = (p.rmax + kMergeRows - 1) / kMergeRows;
+    hipLaunchKernelGGL((attn_merge_wide_kernel<D>), dim3((unsigned)(p.num_seqs * p.hkv * rg)), dim3(512), 0, s, p, rg);
+    return hipGetLastError();
+  }
   // 512 threads: fewer items per thread
   if (p.rmax <= 32)
     hipLaunchKernelGGL((attn_merge_kernel<D, 8>), dim3((unsigned)p.nwaves), dim3(512), 0, s, p);

@@ -38,6 +38,7 @@ struct AttnParams {
 
 constexpr int kAttnHdrInts = 8;           // per-wave header of the partial an item's first wave leaves
 constexpr int kAttnMinTilesPerWave = 2;   // floor of the even split (short batches)
+constexpr int kAttnMinTilesLong = 6;      // and of a head with many tiles over few sequences
 constexpr int kAttnMaxWaves = 1024;       // waves of the even split: one per SIMD of 256 CUs
 // Tiles moved, per 1024, from the share of each pair on an odd XCD to the one on an even XCD:
 // waves on odd XCDs stream the cache a few per cent slower.

@@ -153,6 +153,19 @@ def test_attention_skewed_share_pairs_odd_head_count():
                     ctx=("uniform", 9000, 11000), k=("fixed", 4))
 
 
+@pytest.mark.parametrize("batch,hq,hkv,D,k,lo,hi,chunk", [
+    (1, 4, 1, 128, 4, 2540, 2600, 32),     # 80 shares of one item: a second pass of the merge's 64
+    (1, 8, 1, 64, 7, 5000, 5100, 32),      # 64 rows, 157 to 160 shares (128 a pass at head size 64)
+    (2, 32, 8, 128, 4, 3000, 12000, 0),    # the even split at its longer least share
+    (3, 14, 2, 64, 3, 1, 700, 0),          # 28 rows, items whole, cut once and cut often
+    (1, 3, 1, 128, 0, 40, 90, 32),         # three rows: one of four row slots idle
+])
+def test_attention_few_long_sequences(batch, hq, hkv, D, k, lo, hi, chunk):
+    # few sequences over many shares: the merge that splits an item's contributors over a workgroup
+    check_attention(1, seed=60 + batch + D, batch=batch, num_q_heads=hq, num_kv_heads=hkv, head_dim=D,
+                    ctx=("uniform", lo, hi), k=("fixed", k), kv_chunk_tokens=chunk)
+
+
 def random_attention_geometry(seed):
     """One random attention geometry (seeded; the test's own draw): head size, block size, KV
     heads, group size and draft counts within the boundary's limits (G (k+1) <= 64 rows), batch,
