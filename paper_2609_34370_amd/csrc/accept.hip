@@ -29,6 +29,9 @@
 //     stream  round r, one work item per (sequence of the list, sub-chunk): the job, after one
 //             load of its record.  So the sampled rows of finished sequences stream together
 //             with the next round's rows.
+//   given     (logit inputs whose statistics the caller gives) in place of the rounds' statistics and
+//             tests: one workgroup per sequence reduces its rows' partials and runs every test; then
+//             one stream launch over the sampled rows.
 //   init      (probability inputs) one thread per sequence: geometry, draft-id check, tests.
 //   max pass  (probability inputs) per sub-chunk: max of p, bad flag.
 //   sum pass  (probability inputs) per sub-chunk: the sums of W_v.
@@ -246,15 +249,12 @@ __device__ __forceinline__ RowCtx row_ctx(const AcceptParams& p, int b, const Ge
   r.logits = p.kind == 1;
   r.Mp = r.Rp = r.Mq = r.Rq = 1.f;
   if (r.logits) {
-    // partials computed here (per 4096-entry sub-chunk) or given by the caller (per column tile)
-    const bool ext = p.ext_tstats != nullptr;
-    const int np = ext ? p.ext_parts : p.nsub;
-    const float* lp = ext ? p.ext_tstats + (int64_t)(g.t0 + a) * np * 2 : lse_slot(p, b, a, 0);
-    const float* lq = ext ? p.ext_dstats + (int64_t)(g.d0 + a) * np * 2 : lse_slot(p, b, a, 1);
-    const Part2 fp = part_first(lp, np, lane, -INFINITY, 0.f);
-    const Part2 fq = with_q ? part_first(lq, np, lane, -INFINITY, 0.f) : Part2{-INFINITY, 0.f};
-    row_stats(lp, np, lane, fp, r.Mp, r.Rp);
-    if (with_q) row_stats(lq, np, lane, fq, r.Mq, r.Rq);
+    const float* lp = lse_slot(p, b, a, 0);
+    const float* lq = lse_slot(p, b, a, 1);
+    const Part2 fp = part_first(lp, p.nsub, lane, -INFINITY, 0.f);
+    const Part2 fq = with_q ? part_first(lq, p.nsub, lane, -INFINITY, 0.f) : Part2{-INFINITY, 0.f};
+    row_stats(lp, p.nsub, lane, fp, r.Mp, r.Rp);
+    if (with_q) row_stats(lq, p.nsub, lane, fq, r.Mq, r.Rq);
   }
   return r;
 }
@@ -437,7 +437,7 @@ __device__ __forceinline__ void wave_stats(float (&v)[kPerLane], float c, float&
 
 // Sequence b's rows and state for the tests launches (valid: 1 valid, 0 no query token, -1 a
 // draft id outside [0, V)), written once per sequence by the pass before the first tests launch
-// (the statistics or the gather pass).  That launch then reads one record per sequence instead
+// (the statistics pass).  That launch then reads one record per sequence instead
 // of query_start_loc and every draft id: a dependent round trip less.
 __device__ __forceinline__ void store_geom_state(const AcceptParams& p, int b, const Geom& g, int bad_id) {
   const int state = !g.valid ? 0 : bad_id ? -1 : 1;
@@ -471,13 +471,8 @@ __device__ __forceinline__ void gather_test(const AcceptParams& p, int b, const 
   const int x = p.ids[g.d0 + pos];
   const bool ok = x >= 0 && x < p.V;
   f32x4 t;
-  if (p.tg_given) {   // gathered by the LM head (the same fp32 values)
-    t[0] = ok ? p.tg_given[g.t0 + pos] : 0.f;
-    t[1] = ok ? p.dg_given[g.d0 + pos] : 0.f;
-  } else {
-    t[0] = ok ? p.target[(int64_t)(g.t0 + pos) * p.V + x] : 0.f;
-    t[1] = ok ? p.draft[(int64_t)(g.d0 + pos) * p.V + x] : 0.f;
-  }
+  t[0] = ok ? p.target[(int64_t)(g.t0 + pos) * p.V + x] : 0.f;
+  t[1] = ok ? p.draft[(int64_t)(g.d0 + pos) * p.V + x] : 0.f;
   t[2] = p.u_accept[g.d0 + pos];
   t[3] = ok ? 1.f : 0.f;
   *reinterpret_cast<f32x4*>(p.tin + ((int64_t)b * p.max_k + pos) * 4) = t;
@@ -585,64 +580,123 @@ __global__ __launch_bounds__(kThreads) void accept_stats_kernel(AcceptParams p, 
   }
 }
 
-// Given per-tile statistics of `rows` rows reduced to one (max, sum) per row, one wave per row:
-// M = max over the tiles, then Z = sum of z * 2^(m - M) (lane-strided partial sums, combined
-// across the wave in a fixed order; every consumer reads the reduced pair).  Each lane's tiles
-// are loaded 8 at a time, the loads of a group issued together.
-__global__ __launch_bounds__(kThreads) void accept_combine_kernel(const float* src, int parts, int rows,
-                                                                  float* dst) {
-  constexpr int kG = 8;
-  const int lane = threadIdx.x % kWave;
-  const int row = blockIdx.x * kWaves + threadIdx.x / kWave;
-  if (row >= rows) return;
-  const f32x2* part = reinterpret_cast<const f32x2*>(src + (int64_t)row * parts * 2);
+// Position pos of sequence b will be sampled (logit rows, statistics rc): its job in the stream launch
+// (rec) and the search's record.  Called by one thread.  The scale is the target row's 1/Z; a row whose
+// statistics are not finite is bad, and a bad or empty row has no sums to compute (the search reports
+// it).
+__device__ __forceinline__ void store_sampled(const AcceptParams& p, int b, const Geom& g, int pos, bool residual,
+                                              const RowCtx& rc, u32x4* rec) {
+  const float M = rc.Rp;
+  const int bad = !(rc.Rp > 0.f) || isinf(rc.Rp) || (residual && (!(rc.Rq > 0.f) || isinf(rc.Rq)));
+  const u32x4 stats{__float_as_uint(rc.Mp), __float_as_uint(rc.Rp), __float_as_uint(rc.Mq), __float_as_uint(rc.Rq)};
+  u32x4* srec = reinterpret_cast<u32x4*>(p.srec) + 3 * (int64_t)b;
+  srec[0] = u32x4{(uint32_t)g.t0, (uint32_t)g.d0, (uint32_t)g.k, (uint32_t)pos};
+  srec[1] = u32x4{(uint32_t)(residual ? kResidual : kBonus), (uint32_t)bad, __float_as_uint(M), 0u};
+  srec[2] = stats;
+  const bool go = !bad && M > 0.f;
+  rec[0] = u32x4{(uint32_t)b, (uint32_t)g.t0, (uint32_t)g.d0, (uint32_t)g.k};
+  rec[1] = u32x4{(uint32_t)(go ? (residual ? kJobResidual : kJobBonus) : kJobNone), (uint32_t)pos, 0u,
+                 (uint32_t)(go ? 40 - floor_log2(M) : 0)};
+  rec[2] = stats;
+}
+
+// The statistics of one row from given (max, sum) partials, by one wave: M = the largest maximum, R = the
+// reciprocal of sum z 2^(m - M) (NaN for a row without a finite maximum or with a NaN sum).  Each lane's
+// first kG partials are loaded together and kept; a row of more than 64 kG loads the rest twice.
+__device__ __forceinline__ void given_row_stats(const f32x2* part, int parts, int lane, float& M, float& R) {
+  constexpr int kG = 16;
+  f32x2 v[kG];
+#pragma unroll
+  for (int u = 0; u < kG; ++u) v[u] = part[min(lane + u * kWave, parts - 1)];
   float mm = -INFINITY;
-  for (int x0 = lane; x0 < parts; x0 += kG * kWave) {
-    f32x2 v[kG];
 #pragma unroll
-    for (int u = 0; u < kG; ++u) v[u] = part[min(x0 + u * kWave, parts - 1)];
-#pragma unroll
-    for (int u = 0; u < kG; ++u)
-      if (x0 + u * kWave < parts) mm = fmaxf(mm, v[u][0]);
-  }
+  for (int u = 0; u < kG; ++u)
+    if (lane + u * kWave < parts) mm = fmaxf(mm, v[u][0]);
+  for (int x = lane + kG * kWave; x < parts; x += kWave) mm = fmaxf(mm, part[x][0]);
   mm = wave_max(mm);
   float zz = 0.f;
   int nan = 0;
-  for (int x0 = lane; x0 < parts; x0 += kG * kWave) {
-    f32x2 v[kG];
+  auto add = [&](f32x2 e) {
+    nan |= e[1] != e[1];
+    if (e[0] != -INFINITY) zz += e[1] * fast_exp2(e[0] - mm);
+  };
 #pragma unroll
-    for (int u = 0; u < kG; ++u) v[u] = part[min(x0 + u * kWave, parts - 1)];
-#pragma unroll
-    for (int u = 0; u < kG; ++u) {
-      if (x0 + u * kWave >= parts) continue;
-      nan |= v[u][1] != v[u][1];
-      if (v[u][0] != -INFINITY) zz += v[u][1] * fast_exp2(v[u][0] - mm);
-    }
-  }
+  for (int u = 0; u < kG; ++u)
+    if (lane + u * kWave < parts) add(v[u]);
+  for (int x = lane + kG * kWave; x < parts; x += kWave) add(part[x]);
   zz = wave_sum(zz);
   nan = wave_or(nan);
-  if (lane == 0) *reinterpret_cast<f32x2*>(dst + (int64_t)row * 2) = f32x2{mm, nan ? NAN : zz};
+  M = mm;
+  R = (nan || !(mm > -INFINITY) || !(mm < INFINITY)) ? NAN : 1.0f / zz;
 }
 
-// The inputs of every test, when the statistics are given and no stats pass gathers them.
-__global__ __launch_bounds__(kThreads) void accept_gather_kernel(AcceptParams p) {
-  // one thread per (sequence, draft position); max_k >= 1 (with no drafts there is nothing to
-  // gather or check)
-  const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (idx >= (int64_t)p.B * p.max_k) return;
-  const int b = (int)(idx / p.max_k), i = (int)(idx % p.max_k);
+// Given statistics: everything up to the stream launch in one, one workgroup of 16 waves per sequence.
+// The waves reduce the partials of its 2k + 1 rows, a row each, while lane i of wave 0 gathers the
+// inputs of test i; wave 0 then runs all tests at once and leaves the job and the search's record, as
+// the tests launch does.  (One launch to reduce the target rows, one for the draft rows, one to gather
+// and one to test: 38.7 against 28.5 us for acceptance at 64 sequences of 4 drafts, rows of 1002
+// partials, and 35.6 against 32.2 for a draw, a selection and a look-ahead estimate there.)
+constexpr int kGivenThreads = 1024;
+__global__ __launch_bounds__(kGivenThreads) void accept_given_kernel(AcceptParams p) {
+  constexpr int kGivenWaves = kGivenThreads / kWave;
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const int b = blockIdx.x;
   int n;
   const Geom g = seq_geom(p, b, n);
-  if (i == 0) {
-    int bad = 0;
-    for (int j = 0; j < g.k; ++j) {
-      const int x = p.ids[g.d0 + j];
-      bad |= x < 0 || x >= p.V;
+  const bool tests = wave == 0 && lane < g.k;   // k <= kAcceptMaxK < kWave
+  float tx = 0.f, qx = 0.f, u = 0.f;
+  bool bad_id = false;
+  if (tests) {
+    const int x = p.ids[g.d0 + lane];
+    u = p.u_accept[g.d0 + lane];
+    bad_id = x < 0 || x >= p.V;
+    if (!bad_id) {
+      // gathered by the LM head (the same fp32 values), or from the logit rows
+      tx = p.tg_given ? p.tg_given[g.t0 + lane] : p.target[(int64_t)(g.t0 + lane) * p.V + x];
+      qx = p.tg_given ? p.dg_given[g.d0 + lane] : p.draft[(int64_t)(g.d0 + lane) * p.V + x];
     }
-    store_geom_state(p, b, g, bad);
   }
-  if (!g.valid || i >= g.k) return;
-  gather_test(p, b, g, i);
+  // row j <= k: target row j; then draft row j - k - 1
+  __shared__ float sm_m[2 * kAcceptMaxK + 1], sm_r[2 * kAcceptMaxK + 1];
+  const int rows = g.valid ? 2 * g.k + 1 : 0;   // none of a sequence without a query token
+  for (int j = wave; j < rows; j += kGivenWaves) {
+    const float* base = j <= g.k ? p.ext_tstats + (int64_t)(g.t0 + j) * p.ext_parts * 2
+                                 : p.ext_dstats + (int64_t)(g.d0 + j - g.k - 1) * p.ext_parts * 2;
+    float M, R;
+    given_row_stats(reinterpret_cast<const f32x2*>(base), p.ext_parts, lane, M, R);
+    if (lane == 0) {
+      sm_m[j] = M;
+      sm_r[j] = R;
+    }
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  u32x4* rec = reinterpret_cast<u32x4*>(p.strec) + 3 * (int64_t)b;
+  const bool bad_ids = __ballot(tests && bad_id) != 0;
+  if (!g.valid || bad_ids) {
+    if (lane == 0) {
+      write_invalid(p, b, g.valid ? 1 : 0);
+      rec[1] = u32x4{(uint32_t)kJobNone, 0u, 0u, 0u};
+    }
+    return;
+  }
+  bool fail = false;   // position i fails when !(u_i q_i(x_i) < p_i(x_i)) (NaN statistics fail)
+  if (tests) {
+    const float pp = logit_prob(tx, p.c, sm_m[lane], sm_r[lane]);
+    const float qq = logit_prob(qx, p.c, sm_m[g.k + 1 + lane], sm_r[g.k + 1 + lane]);
+    fail = !((double)u * (double)qq < (double)pp);
+  }
+  const uint64_t failed = __ballot(fail);
+  const int a = failed ? __builtin_ctzll(failed) : g.k;
+  if (lane != 0) return;
+  const bool residual = a < g.k;
+  RowCtx rc;
+  rc.logits = true;
+  rc.Mp = sm_m[a];
+  rc.Rp = sm_r[a];
+  rc.Mq = residual ? sm_m[g.k + 1 + a] : 1.f;
+  rc.Rq = residual ? sm_r[g.k + 1 + a] : 1.f;
+  store_sampled(p, b, g, a, residual, rc, rec);
 }
 
 // Round r, positions [lo, hi), step 1 of 2: one workgroup per sequence of the round's list runs
@@ -699,7 +753,6 @@ __global__ __launch_bounds__(kThreads) void accept_tests_kernel(AcceptParams p, 
     const int a = min(min(sm_fail[0], sm_fail[1]), min(sm_fail[2], sm_fail[3]));
     __syncthreads();
     if (wave != 0) continue;
-    const u32x4 q0 = u32x4{(uint32_t)b, (uint32_t)g.t0, (uint32_t)g.d0, (uint32_t)g.k};
     if (a < g.k || hi > g.k) {
       // a failure at a: the residual of row a; every test passed and the round reached k: the
       // bonus row k.  Either way the scale is known from row a's statistics, which the wave that
@@ -721,26 +774,11 @@ __global__ __launch_bounds__(kThreads) void accept_tests_kernel(AcceptParams p, 
       } else {
         rc = row_ctx(p, b, g, pos, residual, lane);
       }
-      float M;
-      int bad;
-      sampled_scale(p, rc, b, residual, lane, M, bad);
-      if (lane == 0) {
-        const u32x4 stats{__float_as_uint(rc.Mp), __float_as_uint(rc.Rp), __float_as_uint(rc.Mq),
-                          __float_as_uint(rc.Rq)};
-        u32x4* srec = reinterpret_cast<u32x4*>(p.srec) + 3 * (int64_t)b;
-        srec[0] = u32x4{(uint32_t)g.t0, (uint32_t)g.d0, (uint32_t)g.k, (uint32_t)pos};
-        srec[1] = u32x4{(uint32_t)(residual ? kResidual : kBonus), (uint32_t)bad, __float_as_uint(M), 0u};
-        srec[2] = stats;
-        // a bad or empty row has no sums to compute (the search reports it)
-        const bool go = !bad && M > 0.f;
-        rec[0] = q0;
-        rec[1] = u32x4{(uint32_t)(go ? (residual ? kJobResidual : kJobBonus) : kJobNone), (uint32_t)pos, 0u,
-                       (uint32_t)(go ? 40 - floor_log2(M) : 0)};
-        rec[2] = stats;
-      }
+      if (lane == 0) store_sampled(p, b, g, pos, residual, rc, rec);
     } else {
       // hi <= k <= max_k: round r+1 exists (the host passes hi2 > hi)
       if (lane == 0) {
+        const u32x4 q0 = u32x4{(uint32_t)b, (uint32_t)g.t0, (uint32_t)g.d0, (uint32_t)g.k};
         const int at = __hip_atomic_fetch_add(p.counts + r + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         *reinterpret_cast<u32x4*>(p.lists + ((int64_t)r * p.B + at) * 4) = q0;
         rec[0] = q0;
@@ -1066,32 +1104,12 @@ hipError_t launch_accept(const AcceptParams& p, hipStream_t s) {
   const unsigned items = (unsigned)((int64_t)p.B * p.nsub);
   hipError_t e;
   if (p.kind == 1 && p.ext_tstats) {
-    // Statistics given: reduce each row's tiles once (into the statistics area of the
-    // workspace, which the host checked is large enough), gather the tests' inputs, then one
-    // round over every position.
-    AcceptParams q = p;
-    if (p.ext_parts > 1) {
-      q.ext_tstats = p.lse_part;
-      q.ext_dstats = p.lse_part + 2 * (int64_t)p.T;
-      q.ext_parts = 1;
-      hipLaunchKernelGGL(accept_combine_kernel, dim3((unsigned)((p.T + kWaves - 1) / kWaves)), dim3(kThreads), 0, s,
-                         p.ext_tstats, p.ext_parts, p.T, p.lse_part);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      if (p.T > p.B) {
-        hipLaunchKernelGGL(accept_combine_kernel, dim3((unsigned)((p.T - p.B + kWaves - 1) / kWaves)),
-                           dim3(kThreads), 0, s, p.ext_dstats, p.ext_parts, p.T - p.B,
-                           p.lse_part + 2 * (int64_t)p.T);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-      }
-    }
-    if (q.max_k > 0) {
-      const int64_t n = (int64_t)q.B * q.max_k;
-      hipLaunchKernelGGL(accept_gather_kernel, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0,
-                         s, q);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    if ((e = launch_round(q, 0, 0, q.max_k + 1, 0, s)) != hipSuccess) return e;
-    return launch_search(q, s);
+    // Statistics given: every test in one launch, then the sampled rows.
+    hipLaunchKernelGGL(accept_given_kernel, dim3(p.B), dim3(kGivenThreads), 0, s, p);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(accept_stream_kernel, dim3(items), dim3(kThreads), 0, s, p, 0);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    return launch_search(p, s);
   }
   if (p.kind == 1) {
     // Rounds of doubling width.  A round costs a few microseconds of launch and

@@ -390,7 +390,6 @@ int spexis_accept_with_stats(int32_t num_seqs, int32_t vocab, int32_t max_k, flo
   if ((target_gathered == nullptr) != (draft_gathered == nullptr))
     return fail(SPEXIS_ERR_INVALID_ARGUMENT, "spexis_accept_with_stats: give both gathered arrays or neither");
   if (stats_tiles <= 0) return fail(SPEXIS_ERR_INVALID_ARGUMENT, "spexis_accept_with_stats: stats_tiles <= 0");
-  // the per-row reductions of the statistics live in the workspace's statistics area
   if (num_seqs > 0 && max_k >= 0 && total_tokens > (int64_t)num_seqs * (max_k + 1))
     return fail(SPEXIS_ERR_INVALID_ARGUMENT,
                 "spexis_accept_with_stats: total_tokens %d > num_seqs * (max_k + 1)", total_tokens);

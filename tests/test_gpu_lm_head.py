@@ -323,3 +323,54 @@ def test_lm_head_gathers_the_draft_logits(B, K, d):
         d0 = qsl[:-1] - np.arange(B)
         bad = [b for b in range(B) if d0[b] <= 1 < d0[b] + k[b]][0]
         assert outs[1][2].cpu().numpy()[bad] == sx.SPEXIS_ROW_BAD_TOKEN
+
+
+@pytest.mark.parametrize("parts,K,B", [(1, 32, 5), (64, 4, 7), (65, 8, 3), (1023, 3, 4), (1025, 2, 4), (2100, 1, 2)])
+def test_accept_with_given_partials_equals_acceptance_from_logits(parts, K, B):
+    # statistics over `parts` ranges of columns (some empty: maximum -inf, sum 0), ragged drafts up to
+    # K, masked logits, and a last sequence without a query token; decisions as spexis_accept's own on
+    # the same logits, whose statistics differ from these by fp32 rounding (a uniform falls between the
+    # two with probability about 1e-6 a test; the seeds are fixed)
+    rng = np.random.default_rng(100 * parts + K)
+    V = 1900
+    k = rng.integers(0, K + 1, B)
+    k[0] = K
+    qsl = np.concatenate([[0], np.cumsum(k + 1), [np.sum(k + 1)]]).astype(np.int32)
+    T, n = int(qsl[-1]), B + 1
+    g = torch.Generator().manual_seed(parts)
+    tl = torch.randn((T, V), generator=g) * 3
+    tl[:, 5:90] = -float("inf")
+    src = np.concatenate([np.arange(qsl[b], qsl[b] + k[b]) for b in range(B)]).astype(np.int64)
+    dl = tl[src] + 0.5 * torch.randn((len(src), V), generator=g)
+    # one draft row per draft of the batch and (the empty sequence) none: T - n = drafts - 1 rows
+    ids = torch.multinomial(torch.softmax(dl, 1), 1, generator=g).squeeze(1).to(torch.int32)
+    ids, dl = ids[: T - n], dl[: T - n]
+    edges = np.linspace(0, V, parts + 1).astype(np.int64)
+
+    def stats(x):
+        y = x.double() * 1.4426950408889634
+        out = torch.zeros((x.shape[0], parts, 2), dtype=torch.float64)
+        out[:, :, 0] = -float("inf")
+        for i in range(parts):
+            if edges[i] < edges[i + 1]:
+                s = y[:, edges[i]:edges[i + 1]]
+                m = s.amax(1)
+                out[:, i, 0] = m
+                out[:, i, 1] = torch.where(m > -float("inf"), torch.exp2(s - m[:, None]).nan_to_num(0.0).sum(1), 0.0)
+        return out.float().cuda()
+
+    ua, us = torch.rand(T - n, generator=g).cuda(), torch.rand(n, generator=g).cuda()
+    dev = lambda x: torch.as_tensor(x, device="cuda").contiguous()
+    ws = torch.empty(sx.spexis_accept_workspace_size(n, V, K), dtype=torch.uint8, device="cuda")
+    got = []
+    for given in (True, False):
+        o = [torch.full(s, 77, dtype=torch.int32, device="cuda") for s in ((n,), (n, K + 1), (n,))]
+        if given:
+            sx.spexis_accept_with_stats(dev(qsl), dev(tl), dev(dl), stats(tl), stats(dl), dev(ids), ua, us, K, *o, ws)
+        else:
+            sx.spexis_accept(sx.SPEXIS_INPUT_LOGITS, dev(qsl), dev(tl), dev(dl), dev(ids), ua, us, K, *o, ws)
+        torch.cuda.synchronize()
+        got.append([x.cpu().numpy() for x in o])
+    assert (got[0][2][:B] == 0).all() and got[0][2][B] == sx.SPEXIS_ROW_BAD_VALUE
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
