@@ -32,7 +32,9 @@
 //   given     (logit inputs whose statistics the caller gives) in place of the rounds' statistics and
 //             tests: one workgroup per sequence reduces its rows' partials and runs every test; then
 //             one stream launch over the sampled rows.
-//   init      (probability inputs) one thread per sequence: geometry, draft-id check, tests.
+//   (short rows) one launch instead of all of this, a workgroup per sequence: accept_probs_kernel
+//             (probabilities), accept_short_kernel (logits).
+//   init      (probability inputs) one wave per sequence: geometry, draft-id check, tests.
 //   max pass  (probability inputs) per sub-chunk: max of p, bad flag.
 //   sum pass  (probability inputs) per sub-chunk: the sums of W_v.
 //   search    one workgroup per sequence: total, exact threshold, the sub-chunk holding it,
@@ -86,8 +88,10 @@ __device__ __forceinline__ Geom seq_geom(const AcceptParams& p, int b, int& n) {
 
 // p = 2^(x*c - M) * (1/Z): the probability of a logit, the same expression in every pass
 // (R = 1/Z is rounded once per row).  x*c - M is one explicit fused multiply-add, so no site
-// can contract it differently from another: every pass sees the same probabilities.
+// can contract it differently from another: every pass sees the same probabilities.  The product is not
+// contracted into what follows: a difference of two equal probabilities is exactly 0.
 __device__ __forceinline__ float logit_prob(float x, float c, float M, float R) {
+#pragma clang fp contract(off)
   return fast_exp2(__builtin_fmaf(x, c, -M)) * R;
 }
 
@@ -321,6 +325,7 @@ __device__ __forceinline__ void sampled_scale(const AcceptParams& p, const RowCt
 // the search evaluate exactly this expression.
 __device__ __forceinline__ uint64_t entry_weight(const RowCtx& r, float c, float pv_raw, float qv_raw, bool use_p,
                                                  int s) {
+#pragma clang fp contract(off)
   const float P = prob_of(r, pv_raw, c, false);
   float w;
   if (use_p) {
@@ -388,26 +393,41 @@ __device__ void sample_sums(const AcceptParams& p, int b, const Geom& g, int a, 
 
 // ---------------------------------------------------------------------------------- init
 
+// Test inputs of sequence b, lane i of a wave taking test i (k <= kAcceptMaxK < kWave); the result says
+// whether a draft id lies outside the vocabulary.
+struct TestIn {
+  int x;
+  float tx, qx, u;
+};
+__device__ __forceinline__ bool gather_tests(const AcceptParams& p, const Geom& g, int lane, TestIn& t) {
+  t = TestIn{-1, 0.f, 0.f, 0.f};
+  bool bad = false;
+  if (lane < g.k) {
+    t.x = p.ids[g.d0 + lane];
+    t.u = p.u_accept[g.d0 + lane];
+    bad = t.x < 0 || t.x >= p.V;
+    if (!bad) {
+      t.tx = p.target[(int64_t)(g.t0 + lane) * p.V + t.x];
+      t.qx = p.draft[(int64_t)(g.d0 + lane) * p.V + t.x];
+    }
+  }
+  return __ballot(bad) != 0;
+}
+
+// One wave per sequence, a lane per test (one thread per sequence, its gathers one after another, took
+// 9.5 us at 128 sequences of up to 8 drafts).
 __global__ __launch_bounds__(kThreads) void accept_init_kernel(AcceptParams p) {
-  const int b = blockIdx.x * kThreads + threadIdx.x;
+  const int b = blockIdx.x * kWaves + threadIdx.x / kWave, lane = threadIdx.x % kWave;
   if (b >= p.B) return;
   int n;
   const Geom g = seq_geom(p, b, n);
-  bool ok = n >= 1;
-  for (int i = 0; ok && i < g.k; ++i) {
-    const int x = p.ids[g.d0 + i];
-    ok = x >= 0 && x < p.V;
-  }
+  TestIn t;
+  const bool ok = !gather_tests(p, g, lane, t) && n >= 1;
+  const uint64_t failed = __ballot(lane < g.k && !((double)t.u * (double)t.qx < (double)t.tx));
+  if (lane != 0) return;
   *reinterpret_cast<u32x4*>(p.geo + 4 * (int64_t)b) = u32x4{(uint32_t)g.t0, (uint32_t)g.d0, (uint32_t)g.k, ok ? 1u : 0u};
   if (!ok) return write_invalid(p, b, n);
-  int a = 0;
-  while (a < g.k) {
-    const int x = p.ids[g.d0 + a];
-    const double pp = (double)p.target[(int64_t)(g.t0 + a) * p.V + x];
-    const double qq = (double)p.draft[(int64_t)(g.d0 + a) * p.V + x];
-    const double u = (double)p.u_accept[g.d0 + a];
-    if (u * qq < pp) ++a; else break;
-  }
+  const int a = failed ? __builtin_ctzll(failed) : g.k;
   p.st_a[b] = a;
   p.st_mode[b] = a < g.k ? kResidual : kBonus;
 }
@@ -1003,6 +1023,279 @@ __global__ __launch_bounds__(kThreads) void accept_search_kernel(AcceptParams p)
   }
 }
 
+// ------------------------------------------------------------ one launch, a workgroup a sequence
+
+// The sample at position a of sequence b, from the sampled row(s) in the workgroup's registers (thread t
+// holds entries 4 (TH j + t) .. +3, j < F4, of target row a in pv and, for a residual, of draft row a in
+// qv) at the scale M > 0: fixed-point sums, threshold, token, outputs.  ids: lane i of wave 0 holds draft i.
+template <int TH, int F4>
+__device__ __forceinline__ void sample_held(const AcceptParams& p, const RowCtx& r, int b, const Geom& g, int a, float M,
+                                            float us, int ids, const float (&pv)[4 * F4], const float (&qv)[4 * F4],
+                                            int wave, int lane) {
+  constexpr int NW = TH / kWave;
+  constexpr int kPer = (F4 * NW + kWave - 1) / kWave;   // (j, wave) sums per lane
+  __shared__ uint64_t sm_w[2][F4 * NW];
+  const int s = 40 - floor_log2(M);
+  int32_t* orow = p.out_tokens + (int64_t)b * (p.max_k + 1);
+  // the sums of the weights per (j, wave), in vocabulary order; a residual whose weights are all 0 falls
+  // back to p
+  bool use_p = a >= g.k;
+  uint64_t S, excl, own[kPer];
+  for (int pass = 0;; ++pass) {
+#pragma unroll
+    for (int j = 0; j < F4; ++j) {
+      uint64_t w = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        w += entry_weight(r, p.c, pv[4 * j + i], use_p ? 0.f : qv[4 * j + i], use_p, s);
+      w = wave_sum_u64(w);
+      if (lane == 0) sm_w[pass][j * NW + wave] = w;
+    }
+    __syncthreads();
+    uint64_t mine = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      own[i] = lane * kPer + i < F4 * NW ? sm_w[pass][lane * kPer + i] : 0;
+      mine += own[i];
+    }
+    excl = wave_incl_scan_u64(mine);
+    S = readlane_u64(excl, kWave - 1);
+    excl -= mine;
+    if (S != 0 || use_p) break;
+    use_p = true;
+  }
+  // until the thread whose entries hold the threshold overwrites it, the output says that no token was
+  // found (which cannot happen while every sum is of the same weights); the barrier orders the two
+  if (threadIdx.x == 0) {
+    orow[a] = -1;
+    p.accepted_len[b] = a;
+    p.row_status[b] = SPEXIS_ROW_INTERNAL;
+    if (p.tok_prob) p.tok_prob[b] = 0.f;
+  }
+  if (wave == 0)
+    for (int i = lane; i <= p.max_k; i += kWave)
+      if (i != a) orow[i] = i < a ? ids : -1;
+  __syncthreads();
+  const uint64_t t = exact_threshold(us, S);
+  int at = -1;
+  uint64_t tt = 0;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    if (at < 0 && excl <= t && t < excl + own[i]) {
+      at = lane * kPer + i;
+      tt = t - excl;
+    }
+    excl += own[i];
+  }
+  const uint64_t found = __ballot(at >= 0);
+  if (!found) return;   // unreachable: S > 0 (p's largest entry alone weighs >= 2^40)
+  const int src = __builtin_ctzll(found);
+  at = __builtin_amdgcn_readlane(at, src);
+  tt = readlane_u64(tt, src);
+  if (wave != at % NW) return;
+  const int jt = at / NW;
+  uint64_t wv[4] = {0, 0, 0, 0}, mine = 0;
+  float raw[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < F4; ++j) {
+    if (j != jt) continue;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      raw[i] = pv[4 * j + i];
+      wv[i] = entry_weight(r, p.c, pv[4 * j + i], use_p ? 0.f : qv[4 * j + i], use_p, s);
+      mine += wv[i];
+    }
+  }
+  uint64_t pre = wave_incl_scan_u64(mine) - mine;
+  if (!(pre <= tt && tt < pre + mine)) return;
+  int token = -1;
+  float prob = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (token < 0 && tt < pre + wv[i]) {
+      token = 4 * (TH * jt + (int)threadIdx.x) + i;
+      prob = prob_of(r, raw[i], p.c, false);
+    }
+    pre += wv[i];
+  }
+  if (p.tok_prob) p.tok_prob[b] = prob;
+  orow[a] = token;
+  p.row_status[b] = SPEXIS_ROW_OK;
+  if (p.seq_lens_inout) p.seq_lens_inout[b] -= g.k - a;
+}
+
+// load4 with the row's form known at compile time: kVec for V a multiple of 4, whose four entries are
+// all inside or all past the row (one predicate a load instead of five keeps the kernels below free of
+// spilled registers).
+template <bool kVec>
+__device__ __forceinline__ f32x4 load4_of(const float* row, int e, int V, float fill) {
+  if (!kVec) return load4(row, e, V, false, fill);
+  return e < V ? *reinterpret_cast<const f32x4*>(row + e) : f32x4{fill, fill, fill, fill};
+}
+
+// A row of position a into the workgroup's registers, as sample_held takes them.
+template <int TH, int F4, bool kVec>
+__device__ __forceinline__ void hold_row(const float* row, int V, float fill, float (&v)[4 * F4]) {
+#pragma unroll
+  for (int j = 0; j < F4; ++j) {
+    const f32x4 e = load4_of<kVec>(row, 4 * (TH * j + (int)threadIdx.x), V, fill);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[4 * j + i] = e[i];
+  }
+}
+
+// Probability rows of up to 4 TH F4 entries, one workgroup per sequence: the tests need two gathers each
+// and a lane each, then the sampled position's rows are read once, into registers, for their checks, their
+// scale, the sums and the token.  Four launches (tests, maxima, sums, search) read them twice: 29.3 against
+// 20.9 us at 128 sequences of 32000 entries, 4 drafts each.
+template <int TH, int F4, bool kVec>
+__global__ __launch_bounds__(TH) void accept_probs_kernel(AcceptParams p) {
+  constexpr int NW = TH / kWave, NE = 4 * F4;
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const int b = blockIdx.x;
+  int n;
+  const Geom g = seq_geom(p, b, n);
+  TestIn t;
+  const bool bad_ids = gather_tests(p, g, lane, t);
+  if (!g.valid || bad_ids) {
+    if (threadIdx.x == 0) write_invalid(p, b, n);
+    return;
+  }
+  const float us = p.u_sample[b];
+  const uint64_t failed = __ballot(lane < g.k && !((double)t.u * (double)t.qx < (double)t.tx));
+  const int a = failed ? __builtin_ctzll(failed) : g.k;
+  const bool residual = a < g.k;
+  float pv[NE], qv[NE];
+  hold_row<TH, F4, kVec>(p.target + (int64_t)(g.t0 + a) * p.V, p.V, 0.f, pv);
+  if (residual) {
+    hold_row<TH, F4, kVec>(p.draft + (int64_t)(g.d0 + a) * p.V, p.V, 0.f, qv);
+  } else {
+#pragma unroll
+    for (int e = 0; e < NE; ++e) qv[e] = 0.f;
+  }
+  float M = 0.f;
+  bool bad = false;
+#pragma unroll
+  for (int e = 0; e < NE; ++e) {
+    bad |= bad_value(pv[e]) || bad_value(qv[e]);
+    M = pv[e] > M ? pv[e] : M;
+  }
+  __shared__ float sm_max[NW];
+  __shared__ int sm_bad[NW];
+  M = wave_max(M);
+  const int bad_any = __ballot(bad) != 0;
+  if (lane == 0) {
+    sm_max[wave] = M;
+    sm_bad[wave] = bad_any;
+  }
+  __syncthreads();
+  int any = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    M = fmaxf(M, sm_max[w]);
+    any |= sm_bad[w];
+  }
+  if (any || !(M > 0.f)) {
+    if (threadIdx.x == 0) write_outputs(p, b, g, a, -1, any ? SPEXIS_ROW_BAD_VALUE : SPEXIS_ROW_EMPTY);
+    return;
+  }
+  RowCtx r;
+  r.logits = false;
+  r.Mp = r.Rp = r.Mq = r.Rq = 1.f;
+  sample_held<TH, F4>(p, r, b, g, a, M, us, t.x, pv, qv, wave, lane);
+}
+
+// Logit rows of up to kShortRow entries, one workgroup of 16 waves per sequence: a wave per row reduces the
+// statistics of all 2k + 1 rows, wave by wave every test is decided at once, and the sampled rows are
+// read back (from L2) for the sums and the token.  At such sizes the launches cost more than the rows.
+constexpr int kShortRow = 4096, kProbsRow = 32768, kShortThreads = 1024;
+template <bool kVec>
+__global__ __launch_bounds__(kShortThreads) void accept_short_kernel(AcceptParams p) {
+  constexpr int NW = kShortThreads / kWave, kLoads = kShortRow / (4 * kWave);
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const int b = blockIdx.x;
+  int n;
+  const Geom g = seq_geom(p, b, n);
+  TestIn t;
+  const bool bad_ids = gather_tests(p, g, lane, t);
+  if (!g.valid || bad_ids) {
+    if (threadIdx.x == 0) write_invalid(p, b, n);
+    return;
+  }
+  const float us = p.u_sample[b];
+  // row j <= k: target row j; then draft row j - k - 1
+  __shared__ float sm_m[2 * kAcceptMaxK + 1], sm_r[2 * kAcceptMaxK + 1];
+  for (int j = wave; j < 2 * g.k + 1; j += NW) {
+    const float* row = j <= g.k ? p.target + (int64_t)(g.t0 + j) * p.V : p.draft + (int64_t)(g.d0 + j - g.k - 1) * p.V;
+    f32x4 v[kLoads];
+#pragma unroll
+    for (int e = 0; e < kLoads; ++e)
+      v[e] = load4_of<kVec>(row, 4 * (kWave * e + lane), p.V, -INFINITY);
+    float m = -INFINITY, z = 0.f;
+    bool nan = false;   // a NaN or +inf: the row's probabilities are undefined
+#pragma unroll
+    for (int e = 0; e < kLoads; ++e)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        nan |= !(v[e][i] < INFINITY);
+        m = fmaxf(m, v[e][i] * p.c);
+      }
+    m = wave_max(m);
+    if (m != -INFINITY) {
+#pragma unroll
+      for (int e = 0; e < kLoads; ++e)
+        if (4 * kWave * e < p.V)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) z += fast_exp2(__builtin_fmaf(v[e][i], p.c, -m));
+    }
+    z = wave_sum(z);
+    const bool bad = __ballot(nan) != 0 || !(m > -INFINITY) || !(m < INFINITY);
+    if (lane == 0) {
+      sm_m[j] = m;
+      sm_r[j] = bad ? NAN : 1.0f / z;
+    }
+  }
+  __syncthreads();
+  bool fail = false;   // position i fails when !(u_i q_i(x_i) < p_i(x_i)) (NaN statistics fail)
+  if (lane < g.k) {
+    const float pp = logit_prob(t.tx, p.c, sm_m[lane], sm_r[lane]);
+    const float qq = logit_prob(t.qx, p.c, sm_m[g.k + 1 + lane], sm_r[g.k + 1 + lane]);
+    fail = !((double)t.u * (double)qq < (double)pp);
+  }
+  const uint64_t failed = __ballot(fail);
+  const int a = failed ? __builtin_ctzll(failed) : g.k;   // the same in every wave
+  const bool residual = a < g.k;
+  RowCtx r;
+  r.logits = true;
+  r.Mp = sm_m[a];
+  r.Rp = sm_r[a];
+  r.Mq = residual ? sm_m[g.k + 1 + a] : 1.f;
+  r.Rq = residual ? sm_r[g.k + 1 + a] : 1.f;
+  const float M = r.Rp;   // the scale: the target row's largest probability
+  const bool bad = !(r.Rp > 0.f) || isinf(r.Rp) || (residual && (!(r.Rq > 0.f) || isinf(r.Rq)));
+  if (bad || !(M > 0.f)) {
+    if (threadIdx.x == 0) write_outputs(p, b, g, a, -1, bad ? SPEXIS_ROW_BAD_VALUE : SPEXIS_ROW_EMPTY);
+    return;
+  }
+  float pv[4], qv[4] = {0.f, 0.f, 0.f, 0.f};
+  hold_row<kShortThreads, 1, kVec>(p.target + (int64_t)(g.t0 + a) * p.V, p.V, -INFINITY, pv);
+  if (residual) hold_row<kShortThreads, 1, kVec>(p.draft + (int64_t)(g.d0 + a) * p.V, p.V, -INFINITY, qv);
+  sample_held<kShortThreads, 1>(p, r, b, g, a, M, us, t.x, pv, qv, wave, lane);
+}
+
+template <bool kVec>
+static hipError_t launch_one_kernel(const AcceptParams& p, hipStream_t s) {
+  if (p.kind == 1)
+    hipLaunchKernelGGL((accept_short_kernel<kVec>), dim3(p.B), dim3(kShortThreads), 0, s, p);
+  else if (p.V <= 4 * 256 * 4)
+    hipLaunchKernelGGL((accept_probs_kernel<256, 4, kVec>), dim3(p.B), dim3(256), 0, s, p);
+  else if (p.V <= 4 * 1024 * 4)
+    hipLaunchKernelGGL((accept_probs_kernel<1024, 4, kVec>), dim3(p.B), dim3(1024), 0, s, p);
+  else
+    hipLaunchKernelGGL((accept_probs_kernel<1024, 8, kVec>), dim3(p.B), dim3(1024), 0, s, p);
+  return hipGetLastError();
+}
+
 // ------------------------------------------------------------------------------- softmax
 
 __global__ __launch_bounds__(kThreads) void softmax_rows_kernel(const float* logits, float* probs, int V, float c) {
@@ -1103,6 +1396,16 @@ static hipError_t launch_search(const AcceptParams& p, hipStream_t s) {
 hipError_t launch_accept(const AcceptParams& p, hipStream_t s) {
   const unsigned items = (unsigned)((int64_t)p.B * p.nsub);
   hipError_t e;
+  // Short rows: one launch, a workgroup per sequence.  Measured against the launches below: logits at
+  // 1, 128 and 512 sequences of 8 drafts, 10.2, 10.0 and 16.5 against 17.2, 25.0 and 40.7 us with 1000
+  // entries, 10.6, 11.8 and 33.3 against 19.1, 25.5 and 47.2 us with 4096; probabilities (k = 4) 10
+  // against 19 to 25 us up to 4096 entries, 16.4, 20.9 and 51.0 against 19.2, 29.3 and 67.3 us with
+  // 32000.  Rows of more than 16384 entries that are not a multiple of 4 (four loads for one) at few
+  // sequences are better spread over the chip: 29.3 against 24.8 us at 16 sequences of 31999, 32.0
+  // against 38.4 at 128.
+  const bool vec = (p.V & 3) == 0;
+  if (p.kind == 1 ? !p.ext_tstats && p.V <= kShortRow : p.V <= kProbsRow && (vec || p.V <= 16384 || p.B >= 64))
+    return vec ? launch_one_kernel<true>(p, s) : launch_one_kernel<false>(p, s);
   if (p.kind == 1 && p.ext_tstats) {
     // Statistics given: every test in one launch, then the sampled rows.
     hipLaunchKernelGGL(accept_given_kernel, dim3(p.B), dim3(kGivenThreads), 0, s, p);
@@ -1153,7 +1456,7 @@ hipError_t launch_accept(const AcceptParams& p, hipStream_t s) {
       if ((e = launch_round(p, r, lo, hi, hi2, s)) != hipSuccess) return e;
     }
   } else {
-    hipLaunchKernelGGL(accept_init_kernel, dim3((p.B + kThreads - 1) / kThreads), dim3(kThreads), 0, s, p);
+    hipLaunchKernelGGL(accept_init_kernel, dim3((p.B + kWaves - 1) / kWaves), dim3(kThreads), 0, s, p);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(accept_max_kernel, dim3(items), dim3(kThreads), 0, s, p);
     if ((e = hipGetLastError()) != hipSuccess) return e;

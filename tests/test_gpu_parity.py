@@ -752,3 +752,74 @@ def test_empty_batches_return_ok_and_touch_nothing():
     assert (k_pool == 1.5).all() and (v_pool == 1.5).all()
     assert kept_qsl.item() == 77
     say("[empty] every entry point accepted an empty batch")
+
+
+# ------------------------------------------------- short rows: one launch, a workgroup a sequence
+
+@pytest.mark.parametrize("V,B,kmax", [(255, 3, 32), (4095, 9, 5), (4096, 300, 2), (4097, 5, 4), (16384, 7, 3),
+                                      (16388, 3, 8), (16385, 2, 3), (32767, 64, 1), (32768, 4, 6), (32772, 3, 4)])
+def test_accept_row_length_edges(V, B, kmax):
+    # both sides of every length at which the kernel, its width or its loads change: probabilities bit
+    # for bit, logits as the oracle decides (or within 1e-5 of a decision boundary)
+    spec, batch, attn, acc = case(1, seed=5000 + V, batch=B, vocab=V, k=("uniform", 0, kmax), ctx=("uniform", 1, 32),
+                                  draft_noise=("uniform", 0.05, 1.5))
+    p, q = oracle_probs(acc)
+    ids, ua, us = acc.draft_ids.cpu().numpy(), acc.u_accept.cpu().numpy(), acc.u_sample.cpu().numpy()
+    ra, rt, rs, _ = oracle.accept(batch.qsl, p, q, ids, ua, us, max_k=batch.max_k)
+    step = VerifyStep(batch, attn, acc)
+    lens = torch.as_tensor(batch.seq_lens, device="cuda")
+    step.accept(target=torch.as_tensor(p, device="cuda"), draft=torch.as_tensor(q, device="cuda"),
+                kind=sx.SPEXIS_INPUT_PROBS, seq_lens_inout=lens)
+    torch.cuda.synchronize()
+    for got, want in zip(step.accept_outputs(), (ra, rt, rs)):
+        np.testing.assert_array_equal(got, want)
+    np.testing.assert_array_equal(lens.cpu().numpy(), batch.seq_lens - batch.k + ra)
+    step.accept()
+    torch.cuda.synchronize()
+    a, t, s_ = step.accept_outputs()
+    assert (s_ == 0).all()
+    for b in range(batch.B):
+        if a[b] != ra[b] or not np.array_equal(t[b], rt[b]):
+            assert borderline(p, q, ids, ua, us, batch.qsl, b, ra[b], rt[b], a[b], t[b]), b
+
+
+@pytest.mark.parametrize("V", [700, 20004, 40000])
+def test_accept_edge_rows_at_every_length(V):
+    # rows no token can be sampled from, per path: probabilities as the oracle (bit for bit), logits by
+    # the rule that a NaN, +inf or all -inf row has undefined probabilities
+    rng = np.random.default_rng(V)
+    B, K = 9, 2
+    qsl = (np.arange(B + 1) * (K + 1)).astype(np.int32)
+    T = int(qsl[-1])
+    tl = (rng.standard_normal((T, V)) * 2).astype(np.float32)
+    dl = (rng.standard_normal((T - B, V)) * 2).astype(np.float32)
+    p, q = oracle.softmax(tl, 1.0), oracle.softmax(dl, 1.0)
+    ids = rng.integers(0, V, T - B).astype(np.int32)
+    ua, us = np.full(T - B, 0.999, np.float32), rng.random(B, dtype=np.float32)
+    for b in range(B):
+        q[2 * b, ids[2 * b]], dl[2 * b, ids[2 * b]] = 0.9, 30.0   # test 0 rejects ...
+    p[3 * 1, V - 1], tl[3 * 1, V - 1] = np.nan, np.nan
+    p[3 * 2, 3], tl[3 * 2, 3] = np.inf, np.inf
+    p[3 * 3, V // 2], tl[3 * 3] = -0.25, -np.inf
+    p[3 * 4] = 0.0
+    q[2 * 5, 1], dl[2 * 5, 1] = np.nan, np.nan
+    ids[2 * 6 + 1] = V
+    ids[2 * 7] = -1
+    ua[2 * 8: 2 * 8 + 2] = 0.0                                    # ... but not these: the bonus row
+    p[3 * 8 + 2, 7], tl[3 * 8 + 2, 7] = np.nan, np.nan
+    ra, rt, rs, _ = oracle.accept(qsl, p, q, ids, ua, us, max_k=K)
+    dev = lambda x: torch.as_tensor(x, device="cuda")
+    ws = torch.empty(sx.spexis_accept_workspace_size(B, V, K), dtype=torch.uint8, device="cuda")
+    for kind, tg, dr in ((sx.SPEXIS_INPUT_PROBS, p, q), (sx.SPEXIS_INPUT_LOGITS, tl, dl)):
+        o = [torch.full(s, 55, dtype=torch.int32, device="cuda") for s in ((B,), (B, K + 1), (B,))]
+        sx.spexis_accept(kind, dev(qsl), dev(tg), dev(dr), dev(ids), dev(ua), dev(us), K, *o, ws, temperature=1.0)
+        torch.cuda.synchronize()
+        a, t, s_ = (x.cpu().numpy() for x in o)
+        if kind == sx.SPEXIS_INPUT_PROBS:
+            np.testing.assert_array_equal(s_, rs)
+            np.testing.assert_array_equal(a, ra)
+            np.testing.assert_array_equal(t, rt)
+        else:
+            assert s_.tolist() == [0, 2, 2, 2, 0, 2, 3, 3, 2]
+            assert (t[[1, 2, 3, 5, 6, 7]] == -1).all() and a[8] == K and t[8, K] == -1
+            assert (t[[0, 4], 0] >= 0).all() and (t[[0, 4], 0] < V).all()
