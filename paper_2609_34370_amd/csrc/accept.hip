@@ -1298,56 +1298,209 @@ static hipError_t launch_one_kernel(const AcceptParams& p, hipStream_t s) {
 
 // ------------------------------------------------------------------------------- softmax
 
-__global__ __launch_bounds__(kThreads) void softmax_rows_kernel(const float* logits, float* probs, int V, float c) {
-  const int64_t row = blockIdx.x;
-  const float* x = logits + row * V;
-  float* y = probs + row * V;
-  const bool vec = (V & 3) == 0;
-  float m = -INFINITY, s = 0.f;
-  for (int e = 4 * threadIdx.x; e < V; e += 4 * kThreads) {
-    const f32x4 v = load4(x, e, V, vec, -INFINITY);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float t = v[i] * c;
-      if (t > m) {
-        s = s * fast_exp2(m - t) + 1.f;
-        m = t;
-      } else if (t != -INFINITY) {
-        s += fast_exp2(t - m);
-      }
-    }
+// Four values to entries e .. e+3 of a row of V.
+__device__ __forceinline__ void store4(float* row, int e, int V, bool vec, f32x4 o) {
+  if (vec && e + 3 < V) {
+    *reinterpret_cast<f32x4*>(row + e) = o;
+    return;
   }
-  __shared__ float sm_m[kWaves], sm_s[kWaves];
-  const float wm = wave_max(m);
-  float ws = m == -INFINITY ? 0.f : s * fast_exp2(m - wm);
-  ws = wave_sum(ws);
-  if ((threadIdx.x & 63) == 0) {
-    sm_m[threadIdx.x >> 6] = wm;
-    sm_s[threadIdx.x >> 6] = ws;
-  }
-  __syncthreads();
-  const float M = fmaxf(fmaxf(sm_m[0], sm_m[1]), fmaxf(sm_m[2], sm_m[3]));
-  float Z = 0.f;
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) Z += sm_m[w] == -INFINITY ? 0.f : sm_s[w] * fast_exp2(sm_m[w] - M);
-  Z = 1.0f / Z;
-  for (int e = 4 * threadIdx.x; e < V; e += 4 * kThreads) {
-    const f32x4 v = load4(x, e, V, vec, -INFINITY);
-    if (vec && e + 3 < V) {
-      f32x4 o;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) o[i] = logit_prob(v[i], c, M, Z);
-      *reinterpret_cast<f32x4*>(y + e) = o;
-    } else {
-      for (int i = 0; i < 4 && e + i < V; ++i) y[e + i] = logit_prob(v[i], c, M, Z);
-    }
+  for (int i = 0; i < 4; ++i)
+    if (e + i < V) row[e + i] = o[i];
+}
+
+// A thread's entries 4 (TH j + t) .. +3, j < F4, of a row of V (past it: -inf).
+template <int TH, int F4>
+__device__ __forceinline__ void load_run(const float* row, int V, bool vec, float (&v)[4 * F4]) {
+  if (vec) {
+    hold_row<TH, F4, true>(row, V, -INFINITY, v);
+  } else {
+    hold_row<TH, F4, false>(row, V, -INFINITY, v);
   }
 }
 
+// Sum of 2^(x c - M) over a thread's values, the expression of the output (a value of -inf adds 0; with no
+// finite maximum the sum is NaN, or the row is all -inf and its output NaN either way).
+template <int N>
+__device__ __forceinline__ float exp_sum(const float (&v)[N], float c, float M) {
+  float z = 0.f;
+#pragma unroll
+  for (int e = 0; e < N; ++e) z += fast_exp2(__builtin_fmaf(v[e], c, -M));
+  return z;
+}
+
+// Maximum, and sum, over a workgroup's threads.
+template <int NW>
+__device__ __forceinline__ float block_max(float m, float* sm, int wave, int lane) {
+  m = wave_max(m);
+  if (lane == 0) sm[wave] = m;
+  __syncthreads();
+  float r = sm[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) r = fmaxf(r, sm[w]);
+  return r;
+}
+template <int NW>
+__device__ __forceinline__ float block_sum(float z, float* sm, int wave, int lane) {
+  z = wave_sum(z);
+  if (lane == 0) sm[wave] = z;
+  __syncthreads();
+  float r = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) r += sm[w];
+  return r;
+}
+
+// Softmax of one row per workgroup.  The row's first 4 TH F4 entries stay in the threads' registers between
+// the statistics and the output, so rows of up to that many are read once; the entries past them (kTail)
+// are read again, mostly from the last-level cache.  (256 threads that read every row twice, against this:
+// 48.7 against 29.3 us at 520 rows of 32000 entries, 4.5 TB/s, what a large copy reaches; 322 against 244
+// us at 1024 of 128256; holding 32 entries a thread of those instead of 64: 276 us.)
+template <int TH, int F4, bool kTail>
+__global__ __launch_bounds__(TH) void softmax_rows_kernel(const float* logits, float* probs, int V, float c) {
+  constexpr int NW = TH / kWave, kHeld = 4 * TH * F4;
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const float* x = logits + (int64_t)blockIdx.x * V;
+  float* y = probs + (int64_t)blockIdx.x * V;
+  const bool vec = (V & 3) == 0;
+  __shared__ float sm_m[NW], sm_z[NW];
+  float v[4 * F4];
+  load_run<TH, F4>(x, V, vec, v);
+  float m = -INFINITY, z = 0.f;
+#pragma unroll
+  for (int e = 0; e < 4 * F4; ++e) m = fmaxf(m, v[e] * c);
+  if (kTail) {
+    // the tail's own maximum and sum as it streams, against a running maximum
+    float tm = -INFINITY, tz = 0.f;
+    for (int e = kHeld + 4 * (int)threadIdx.x; e < V; e += 4 * TH) {
+      const f32x4 w = load4(x, e, V, vec, -INFINITY);
+      const float wm = fmaxf(fmaxf(w[0], w[1]), fmaxf(w[2], w[3])) * c;
+      if (wm > tm) {
+        tz *= fast_exp2(tm - wm);
+        tm = wm;
+      }
+      if (tm != -INFINITY)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) tz += fast_exp2(__builtin_fmaf(w[i], c, -tm));
+      else
+#pragma unroll
+        for (int i = 0; i < 4; ++i) tz += w[i] != w[i] ? w[i] : 0.f;   // NaN stays NaN
+    }
+    const float M = block_max<NW>(fmaxf(m, tm), sm_m, wave, lane);
+    z = exp_sum(v, c, M) + (tm == -INFINITY ? tz : tz * fast_exp2(tm - M));
+    m = M;
+  } else {
+    m = block_max<NW>(m, sm_m, wave, lane);
+    z = exp_sum(v, c, m);
+  }
+  const float R = 1.0f / block_sum<NW>(z, sm_z, wave, lane);
+#pragma unroll
+  for (int j = 0; j < F4; ++j) {
+    const f32x4 o = {logit_prob(v[4 * j], c, m, R), logit_prob(v[4 * j + 1], c, m, R),
+                     logit_prob(v[4 * j + 2], c, m, R), logit_prob(v[4 * j + 3], c, m, R)};
+    store4(y, 4 * (TH * j + (int)threadIdx.x), V, vec, o);
+  }
+  if (kTail)
+    for (int e = kHeld + 4 * (int)threadIdx.x; e < V; e += 4 * TH) {
+      const f32x4 w = load4(x, e, V, vec, -INFINITY);
+      store4(y, e, V, vec, f32x4{logit_prob(w[0], c, m, R), logit_prob(w[1], c, m, R), logit_prob(w[2], c, m, R),
+                                 logit_prob(w[3], c, m, R)});
+    }
+}
+
+// Few long rows: kSoftmaxChunk entries per workgroup instead of a row, in two launches.  The first leaves
+// each chunk's (maximum, sum) in the output itself, at the start of every chunk of the row (chunk j's copy of
+// partial i at entries 2 i, 2 i + 1 of chunk j), so that the second, whose workgroup overwrites its chunk only
+// after it has read its copies, needs no workspace and waits for no other workgroup.  (So the output must
+// not overlap the input.)
+__device__ __forceinline__ void chunk_range(int V, int chunks, int i, int& lo, int& hi) {
+  const int size = ((V + chunks - 1) / chunks + 3) & ~3;
+  lo = min(V, i * size);
+  hi = min(V, lo + size);
+}
+template <int TH, int F4>
+__global__ __launch_bounds__(TH) void softmax_chunk_stats_kernel(const float* logits, float* probs, int V, int chunks,
+                                                                 float c) {
+  constexpr int NW = TH / kWave;
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const int64_t row = blockIdx.x / chunks;
+  const int ch = blockIdx.x % chunks;
+  int lo, hi;
+  chunk_range(V, chunks, ch, lo, hi);
+  __shared__ float sm_m[NW], sm_z[NW];
+  float v[4 * F4];
+  load_run<TH, F4>(logits + row * V + lo, hi - lo, (V & 3) == 0, v);
+  float m = -INFINITY;
+#pragma unroll
+  for (int e = 0; e < 4 * F4; ++e) m = fmaxf(m, v[e] * c);
+  m = block_max<NW>(m, sm_m, wave, lane);
+  float z = 0.f;
+  if (m != -INFINITY) {
+    z = exp_sum(v, c, m);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4 * F4; ++e) z += v[e] != v[e] ? v[e] : 0.f;   // NaN stays NaN
+  }
+  z = block_sum<NW>(z, sm_z, wave, lane);
+  for (int j = threadIdx.x; j < chunks; j += TH) {
+    int jlo, jhi;
+    chunk_range(V, chunks, j, jlo, jhi);
+    float* at = probs + row * V + jlo + 2 * ch;
+    at[0] = m;
+    at[1] = z;
+  }
+}
+template <int TH, int F4>
+__global__ __launch_bounds__(TH) void softmax_chunk_kernel(const float* logits, float* probs, int V, int chunks,
+                                                           float c) {
+  const int lane = threadIdx.x % kWave;
+  const int64_t row = blockIdx.x / chunks;
+  int lo, hi;
+  chunk_range(V, chunks, blockIdx.x % chunks, lo, hi);
+  const bool vec = (V & 3) == 0;
+  float* y = probs + row * V + lo;
+  float v[4 * F4];
+  load_run<TH, F4>(logits + row * V + lo, hi - lo, vec, v);
+  // every wave combines the row's partials alike: lane i takes partial i (chunks <= 64)
+  const float pm = lane < chunks ? y[2 * lane] : -INFINITY, pz = lane < chunks ? y[2 * lane + 1] : 0.f;
+  const float M = wave_max(pm);
+  const float R = 1.0f / wave_sum(pm == -INFINITY ? pz : pz * fast_exp2(pm - M));
+  __syncthreads();   // every wave has read the copies
+#pragma unroll
+  for (int j = 0; j < F4; ++j) {
+    const f32x4 o = {logit_prob(v[4 * j], c, M, R), logit_prob(v[4 * j + 1], c, M, R),
+                     logit_prob(v[4 * j + 2], c, M, R), logit_prob(v[4 * j + 3], c, M, R)};
+    store4(y, 4 * (TH * j + (int)threadIdx.x), hi - lo, vec, o);
+  }
+}
+
+template <int TH, int F4, bool kTail>
+static hipError_t launch_softmax_rows(const float* logits, float* probs, int64_t rows, int V, float c, hipStream_t s) {
+  hipLaunchKernelGGL((softmax_rows_kernel<TH, F4, kTail>), dim3((unsigned)rows), dim3(TH), 0, s, logits, probs, V, c);
+  return hipGetLastError();
+}
+
+constexpr int kSoftmaxChunk = 4096;   // entries of a chunk, at most (256 threads of 16)
 hipError_t launch_softmax(const float* logits, float* probs, int64_t rows, int V, float c, hipStream_t s) {
   if (rows == 0) return hipSuccess;
-  hipLaunchKernelGGL(softmax_rows_kernel, dim3((unsigned)rows), dim3(kThreads), 0, s, logits, probs, V, c);
-  return hipGetLastError();
+  // Few long rows go by chunks: 10.7, 17.4 and 39.4 against 19.2, 25.8 and 38.7 us at 9, 64 and 128 rows of
+  // 128256 entries, 10.4 against 10.7 us at 64 of 60000 and, at a length that is not a multiple of 4, 63.6
+  // against 95.2 us at 128 of 152063 (121.9 against 115.9 at 256).
+  const bool overlap = logits < probs + rows * V && probs < logits + rows * V;
+  const int chunks = (V + kSoftmaxChunk - 4) / (kSoftmaxChunk - 4);
+  if (V > 65536 && rows <= ((V & 3) == 0 ? 96 : 128) && chunks <= kWave && !overlap) {
+    const dim3 g((unsigned)(rows * chunks));
+    hipLaunchKernelGGL((softmax_chunk_stats_kernel<256, 4>), g, dim3(256), 0, s, logits, probs, V, chunks, c);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((softmax_chunk_kernel<256, 4>), g, dim3(256), 0, s, logits, probs, V, chunks, c);
+    return hipGetLastError();
+  }
+  if (V <= 4096) return launch_softmax_rows<256, 4, false>(logits, probs, rows, V, c, s);
+  if (V <= 16384) return launch_softmax_rows<1024, 4, false>(logits, probs, rows, V, c, s);
+  if (V <= 32768) return launch_softmax_rows<1024, 8, false>(logits, probs, rows, V, c, s);
+  if (V <= 65536) return launch_softmax_rows<1024, 16, false>(logits, probs, rows, V, c, s);
+  return launch_softmax_rows<1024, 16, true>(logits, probs, rows, V, c, s);
 }
 
 // Tests, then stream, of round r.  Later rounds, whose size the host does not know, have

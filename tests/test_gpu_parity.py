@@ -823,3 +823,36 @@ def test_accept_edge_rows_at_every_length(V):
             assert s_.tolist() == [0, 2, 2, 2, 0, 2, 3, 3, 2]
             assert (t[[1, 2, 3, 5, 6, 7]] == -1).all() and a[8] == K and t[8, K] == -1
             assert (t[[0, 4], 0] >= 0).all() and (t[[0, 4], 0] < V).all()
+
+
+@pytest.mark.parametrize("rows,V", [(3, 1), (5, 4096), (2, 4097), (3, 16384), (3, 16388), (2, 32768), (2, 32772),
+                                    (2, 65536), (3, 65537), (96, 65540), (97, 65540), (2, 70001), (129, 65541),
+                                    (1, 261000), (1, 262000)])
+def test_softmax_row_length_edges(rows, V):
+    # both sides of every length and row count at which the kernel changes, into another tensor and in
+    # place, with masked entries and with rows whose probabilities are undefined (all NaN, as one NaN,
+    # +inf or nothing but -inf makes them); 1e-5 is the bar of the softmax tests above
+    g = torch.Generator().manual_seed(rows + V)
+    x = torch.randn((rows, V), generator=g) * 4
+    x[:, 1::7] = -float("inf")
+    bad = {}
+    if rows >= 3:
+        x[1, V - 1] = float("nan")
+        x[2, V // 2] = float("inf")
+        bad = {1, 2}
+    if rows >= 5:
+        x[3] = -float("inf")
+        bad.add(3)
+    ok = [r for r in range(rows) if r not in bad]
+    want = torch.softmax(x.double() / 0.8, dim=1)[ok]
+    d = x.cuda()
+    out = torch.full((rows, V), 7.0, device="cuda")
+    sx.spexis_softmax_rows(d, out, 0.8)
+    assert torch.equal(d.cpu().nan_to_num(9.0), x.nan_to_num(9.0))
+    sx.spexis_softmax_rows(d, d, 0.8)
+    torch.cuda.synchronize()
+    for got in (out.cpu(), d.cpu()):
+        assert (got.double()[ok] - want).abs().max() <= 1e-5 * want.max()
+        assert abs(got.double()[ok].sum(1) - 1).max() <= 1e-5
+        for r in bad:
+            assert torch.isnan(got[r]).all()
