@@ -393,8 +393,8 @@ size_t spexis_linear_workspace_size(int32_t rows, int32_t out_features, int32_t 
  * order (spexis_pack_weight of the stacked rows), and output i receives its columns of x W^T:
  *   y_i[r][o] = bf16( sum_j x[r][j] * W[c_i + o][j] ),   c_i = out_features[0] + ... + [i-1]
  * with fp32 accumulation (the order over j is the library's) and one round to nearest even; no
- * residual.  One projection launch and one launch that adds the K-split partials and routes each
- * layer's columns: at few rows, where each launch is latency-bound, fewer launches than one
+ * residual.  One launch computes and routes all columns (large layers: a projection, and a launch that
+ * adds the K-split partials and routes each layer's columns): at few rows, where each launch is latency-bound, fewer launches than one
  * spexis_linear per layer.
  *   x            [rows][in_features] bf16
  *   num_outputs  1 .. 4;  out_features: host [num_outputs], each > 0 and a multiple of 4

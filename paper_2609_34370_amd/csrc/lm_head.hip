@@ -7,7 +7,8 @@
 // Acceptance combines the tiles of a row into its normaliser without reading the row again.
 //
 // Work decomposition: one workgroup per (vocabulary tile of 256 columns, or 128 for narrow
-// outputs; group of up to 192 rows of h, or all of up to 128 rows); its four waves split the
+// outputs), all of up to 128 rows of h (more rows take the kernels below, but for
+// K splits); its four waves split the
 // tile in a grid of waves (below), each holding 32x32 accumulator tiles of
 // v_mfma_f32_32x32x16_bf16 (A operand: h rows, B operand: W rows).
 //   * W, the stream that matters (V*d*2 bytes, read once), goes straight from HBM into each
@@ -72,6 +73,13 @@ __device__ __forceinline__ void tie(u32x4& v) { asm volatile("" : "+v"(v)); }
 __device__ __forceinline__ void buffer_load_lds16(__amdgpu_buffer_rsrc_t rs, __attribute__((address_space(3))) void* lds,
                                                   int voff, int soff) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, lds, 16, voff, soff, 0, 0);
+}
+
+__device__ __forceinline__ u32x4 buffer_ld16(__amdgpu_buffer_rsrc_t rs, int voff, int soff) {
+  return __builtin_amdgcn_raw_buffer_load_b128(rs, voff, soff, 0);
+}
+__device__ __forceinline__ u32x4 buffer_ld16_nt(__amdgpu_buffer_rsrc_t rs, int voff, int soff) {
+  return __builtin_amdgcn_raw_buffer_load_b128(rs, voff, soff, 2);
 }
 
 // W rows are read once: non-temporal loads keep them from evicting h out of L2.
@@ -384,8 +392,8 @@ void lm_head_kernel(LmParams p) {
 }
 
 // More than 160 rows of a wide projection (an LM head's vocabulary): one workgroup of eight waves
-// (two per SIMD) per (256-column tile, group of 320 rows), so that each K-slice of W crosses L2
-// once per 320 rows.  Both operands go through LDS: every K-step of 64 the
+// (two per SIMD) per (256-column tile, group of 64 RT rows; figures here are of 320), so that each
+// K-slice of W crosses L2 once per group.  Both operands go through LDS: every K-step of 64 the
 // workgroup copies h (320 rows, 40 KB) and W (eight packed 32-column tiles, 32 KB) from memory
 // straight into one of two stages, a step ahead, and the waves read their fragments from the
 // stage, those of the next MFMA step while the current step's MFMAs run.  Wave (wr, wc) of a
@@ -574,6 +582,170 @@ void lm_head_wide_kernel(LmParams p) {
                                      sm_m, sm_z);
 }
 
+// Many rows, in groups of 32 RT: half the waves and rows of lm_head_wide_kernel's workgroup and two
+// workgroups per CU, so that one's epilogue (statistics, 320 of 4250 us at 4608 x 3584 @ 152064) and
+// barriers pass under the other's MFMAs, and a row count is padded to groups half as tall.  h goes
+// through LDS as there; the four waves lie side by side, so no two share a column of W, and W goes
+// straight into registers.  Its bound is power: the matrix cores are busy 96% of the cycles of the K
+// loop, at 1.46 GHz (lm_head_wide_kernel: 86% at 1.64 GHz, the same 1.4 PFLOP/s), so what is left to
+// gain is what does not multiply.  A single group streams W past the caches (kStream: 202 against 221 us
+// at 160 x 4096 @ 128256).
+template <int RT, bool kStream>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+void lm_head_pair_kernel(LmParams p) {
+  constexpr int CT = 2, WC = 4;       // column tiles of a wave, waves
+  constexpr int kRows = 32 * RT;      // rows of the group
+  constexpr int kCols = 32 * WC * CT; // columns of the workgroup
+  // the wave index wave-uniform (scalar), so the copies' LDS destinations are scalar sums
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
+  const int wgcols = (p.V + kCols - 1) / kCols;
+  int nt, mg;
+  tile_of(blockIdx.x, wgcols, p.mgroups, nt, mg);
+  if (nt >= wgcols) return;
+  const int n0 = nt * kCols, m0 = mg * kRows;
+  const int rows = min(kRows, p.M - m0);
+  const int nsteps = p.d / kLmK;
+  const int wtiles = (p.V + 31) / 32;
+  const uint16_t* hbase = reinterpret_cast<const uint16_t*>(p.h) + (int64_t)m0 * p.d;
+  const uint16_t* wbase = reinterpret_cast<const uint16_t*>(p.w);
+
+  // stage x of h: row r, chunk kc (8 K values) at r * 8 + (kc ^ ((r >> 1) & 7)), as above; copied from
+  // memory straight into the stage (1 KB per wave and instruction).  Buffer resources span the group's
+  // rows of h and the workgroup's packed W tiles: loads past them return zeros, whose results are dropped.
+  constexpr int kHStage = kRows * 8;
+  static_assert(2 * kHStage >= WC * 32 * 36 / 4, "the epilogue transposes a tile per wave through the stages");
+  __shared__ u32x4 sm[2 * kHStage];
+  constexpr int kCopies = kHStage / 64 / WC;   // copy instructions per wave and step
+  static_assert(kHStage % (64 * WC) == 0, "copy split");
+  const int wt0 = n0 / 32, wtn = min(kCols / 32, wtiles - wt0);   // the workgroup's packed tiles (a resource per wave spills registers)
+  const __amdgpu_buffer_rsrc_t hrs =
+      __builtin_amdgcn_make_buffer_rsrc((void*)hbase, (short)0, rows * p.d * 2, 0x00020000);
+  const int wtile = nsteps * kPackTile;   // elements of a packed tile
+  const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(wbase + (int64_t)wt0 * wtile), (short)0, wtn * wtile * 2, 0x00020000);
+  int hoff[kCopies], woff[CT];   // byte offsets of the lane's chunks at step 0
+#pragma unroll
+  for (int u = 0; u < kCopies; ++u) {
+    const int q = (wave * kCopies + u) * 64 + lane;
+    const int r = q >> 3, kc = (q & 7) ^ ((r >> 1) & 7);
+    hoff[u] = (r * p.d + 8 * kc) * 2;
+  }
+#pragma unroll
+  for (int c = 0; c < CT; ++c) woff[c] = (CT * wave + c) * wtile * 2 + lane * 16;
+  // copy instruction u of step j
+  auto copy_one = [&](int j, int stage, int u) {
+    buffer_load_lds16(hrs, (__attribute__((address_space(3))) void*)(sm + stage * kHStage + (wave * kCopies + u) * 64),
+                      hoff[u], j * kLmK * 2);
+  };
+  auto copy_step = [&](int j, int stage) {
+#pragma unroll
+    for (int u = 0; u < kCopies; ++u) copy_one(j, stage, u);
+  };
+
+  f32x16 acc[RT][CT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[t][c][e] = 0.f;
+
+  // h fragments by instructions, as in lm_head_wide_kernel; W's by buffer loads, those of step j + 1 into
+  // the registers whose MFMAs of step j have just been issued: in flight for three quarters of a step.
+  static_assert(RT <= 15, "one lgkmcnt covers a step's fragment reads");
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) u32x4*)sm;   // LDS byte address
+  uint32_t aaddr[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+    aaddr[s] = lds0 + col * 128 + (((4 * half + s) ^ ((col >> 1) & 7)) << 4);
+  u32x4 fa[2][RT], fb[4][CT];
+  auto load_w = [&](int j, int s) {
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+      const int off = woff[c] + s * 1024;
+      fb[s][c] = kStream ? buffer_ld16_nt(wrs, off, j * kPackTile * 2) : buffer_ld16(wrs, off, j * kPackTile * 2);
+    }
+  };
+  auto frags = [&](auto stage, auto step) {   // of MFMA step `step` of a stage, into set step % 2
+    constexpr int st = decltype(stage)::value, sp = decltype(step)::value;
+    for_constants<RT>([&](auto t) { fa[sp & 1][t] = lds_read_b128<st * kHStage * 16 + t * 4096>(aaddr[sp]); });
+  };
+  // tie the fragments to the wait, so that no use of them moves above it
+  auto tie_frags = [&](int x) {
+#pragma unroll
+    for (int t = 0; t < RT; ++t) tie(fa[x][t]);
+  };
+  auto mfma_one = [&](int x, int s, int t, int c) {
+    acc[t][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fa[x][t]), as_bf16x8(fb[s][c]), acc[t][c], 0, 0, 0);
+  };
+
+  // Step j, its barrier and the copies as in lm_head_wide_kernel.  The copies of step j + 1 were issued
+  // in step j - 1 before that step's last loads of W and this step's first three: those may stay in flight.
+  auto k_step = [&](auto stage, auto more, auto copy, int j) {
+    constexpr int st = decltype(stage)::value;
+    for_constants<3>([&](auto s) {
+      frags(stage, std::integral_constant<int, s + 1>{});
+      wait_lgkm<RT>();   // this step's reads done; the next step's stay in flight
+      tie_frags(s & 1);
+#pragma unroll
+      for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) mfma_one(s & 1, s, t, c);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (decltype(more)::value) load_w(j + 1, s);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    wait_lgkm<0>();
+    tie_frags(1);
+    if constexpr (decltype(more)::value) {
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * CT) : "memory");
+      __builtin_amdgcn_s_barrier();
+      frags(std::integral_constant<int, st ^ 1>{}, std::integral_constant<int, 0>{});
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < RT * CT || u < kCopies; ++u) {
+      if (u < RT * CT) mfma_one(1, 3, u / CT, u % CT);
+      __builtin_amdgcn_sched_barrier(0);
+      if (decltype(copy)::value && u < kCopies) copy_one(j + 2, st, u);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (decltype(more)::value) load_w(j + 1, 3);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  using Stage0 = std::integral_constant<int, 0>;
+  using Stage1 = std::integral_constant<int, 1>;
+  copy_step(0, 0);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  copy_step(1, 1);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int s = 0; s < 4; ++s) load_w(0, s);
+  __builtin_amdgcn_sched_barrier(0);
+  frags(Stage0{}, Stage0{});
+  int j = 0;   // an even number of steps, at least four (d is a multiple of 256)
+  for (; j + 2 < nsteps; j += 2) {
+    k_step(Stage0{}, std::true_type{}, std::true_type{}, j);
+    k_step(Stage1{}, std::true_type{}, std::true_type{}, j + 1);
+  }
+  k_step(Stage0{}, std::true_type{}, std::false_type{}, j);
+  k_step(Stage1{}, std::false_type{}, std::false_type{}, j + 1);
+  __syncthreads();   // the epilogue's transposes reuse the h stages
+
+  // ---- epilogue (the gather columns first, as above)
+  int gcol[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) gcol[t] = p.gout && p.stats && 32 * t + col < rows ? p.gcols[m0 + 32 * t + col] : -1;
+  store_epilogue<RT, CT, 1, WC>(acc, p.logits, reinterpret_cast<uint16_t*>(p.y),
+                                reinterpret_cast<const uint16_t*>(p.res), p.V, m0, n0, rows, 0, wave, lane);
+  if (!p.stats) return;
+  __shared__ float sm_m[WC][kRows], sm_z[WC][kRows];   // the transposes: the (now free) h stages
+  row_stats_epilogue<RT, CT, 1, WC>(p.stats, p.gout, p.c, p.V, p.ntiles, acc, gcol, nt, m0, n0, rows, 0, wave, lane,
+                                    reinterpret_cast<float*>(&sm[0]), sm_m, sm_z);
+}
+
 template <int RT, int CT, int WR, int NA, int DEPTH, int WPE>
 static hipError_t launch_lm_nrt(const LmParams& q, hipStream_t s) {
   // grid: tiles of 8 vocabulary tiles (one per XCD) x row groups of 32 WR RT rows, row groups
@@ -590,32 +762,46 @@ static hipError_t launch_lm_nrt(const LmParams& q, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Row groups of the many-row shape: 192 rows (six tiles) when that pads M to at most 5% more rows
-// than groups of 160 (five tiles), else 160.  The larger group makes about 10% fewer L2 requests
-// per output (measured 4.73 against 4.98 ms at 4608 x 3584 @ 152064); 320 rows keep two groups
-// of 160 rather than two of 192.
-static int64_t group_rows(int64_t M) {
-  const int64_t p160 = (M + 159) / 160 * 160, p192 = (M + 191) / 192 * 192;
-  return p192 * 20 <= p160 * 21 ? 192 : 160;
-}
-
-// The eight-wave kernel takes 161 to 320 rows (one group), and more rows in groups of 320 when
-// those pad M by no more than its speed per row makes up for: it ran 12% faster than the
-// four-wave groups of 192 at 4608 x 3584 @ 152064 (4273 against 4885 us without logits), so it
-// is taken while its padded rows stay within 1.12 times theirs.
-static bool wide_rows(int64_t M) {
-  const int64_t g = group_rows(M);
-  return M <= 320 || (M + 319) / 320 * 320 * 100 <= (M + g - 1) / g * g * 112;
-}
-
 // Up to 128 rows, 256-column workgroups when the columns alone give at least one workgroup per
 // CU (an LM head's vocabulary); narrower outputs (hidden-size projections) keep 128 columns, whose
 // twice as many workgroups the K split then fills the chip with.
 static bool wide_columns(int64_t M, int64_t N) { return M > 128 || (N + 255) / 256 >= 256; }
 
+// More than 128 rows: the kernel and the rows of its groups.  129 to 160 rows are one group of
+// lm_head_pair_kernel, 161 to 320 one of lm_head_wide_kernel with the smallest of three heights that holds
+// them (at 4096 @ 128256, against groups of 160 of lm_head_kernel, resp. one of 320: 199 against 228 us at
+// 160 rows, 246 against 285 at 192, 280 against 305 at 256).  More rows take the least total of one
+// group's measured time times the groups: 100 for 320 rows of the wide kernel, 51 and 42 for 160 and 128
+// of the pair kernel (against lm_head_kernel or groups of 320: 395 against 464 us at 384 rows, 462 against
+// 574 at 480, 507 against 561 at 512, 1018 against 1143 at 1024 x 3584 @ 152064, 4240 against 4303 at 4608
+// rows there; 640 rows keep 320: 596, with 160 610; 352 rows @ 32000 are level, 104).
+struct RowGroups {
+  bool wide;
+  int rows;
+};
+static RowGroups row_groups(int64_t M) {
+  if (M <= 160) return {false, 160};
+  if (M <= 320) return {true, M <= 192 ? 192 : M <= 256 ? 256 : 320};
+  const int64_t w320 = (M + 319) / 320 * 100, p160 = (M + 159) / 160 * 51, p128 = (M + 127) / 128 * 42;
+  if (w320 <= p160 && w320 <= p128) return {true, 320};
+  return {false, p160 <= p128 ? 160 : 128};
+}
+
+// Row groups of lm_head_kernel, which keeps K splits (and their odd step counts): 192 rows (six tiles) when
+// that pads M to at most 5% more rows than groups of 160 (five tiles), else 160.
+static int64_t group_rows(int64_t M) {
+  const int64_t p160 = (M + 159) / 160 * 160, p192 = (M + 191) / 192 * 192;
+  return p192 * 20 <= p160 * 21 ? 192 : 160;
+}
+
+// The groups that a K split is sized by (one of 320 rows where those pad M little).
+static bool wide_rows(int64_t M) {
+  const int64_t g = group_rows(M);
+  return M <= 320 || (M + 319) / 320 * 320 * 100 <= (M + g - 1) / g * g * 112;
+}
+
 int64_t projection_workgroups(int64_t M, int64_t N) {
-  // the shapes launch_projection picks: one row group up to 128 rows, groups of 160 or 192 rows
-  // beyond
+  // one row group up to 128 rows
   const int64_t cols = wide_columns(M, N) ? (N + 255) / 256 : (N + kLmCols - 1) / kLmCols;
   if (M <= 128) return cols;
   if (M > 160 && wide_rows(M)) return cols * ((M + 319) / 320);
@@ -627,12 +813,10 @@ hipError_t launch_projection(const LmParams& p, hipStream_t s) {
   // group of fewer rows repeats its last row in the padding tiles, whose results are dropped).
   // Wide shapes are 256 columns: four waves across, each two column tiles of 32 (wide_columns).
   // Up to 64 rows, a hint of two waves per SIMD; more rows take more accumulators and one.
-  // Beyond 128 rows, groups of 160 or 192 rows (group_rows).  Every load -- h from L2, W from
-  // HBM -- is an L1 miss, and each CU's capacity for pending misses bounds the streams, so wider
-  // tiles' fewer requests per MFMA pay: at 4096 @ 128256, 180 against 188 us for 128-column
-  // workgroups at 32 rows, 190 against 205 at 64, 215 against 265 at 128, and at 320 rows 437
-  // against 460 us for 320 x 128 workgroups on a 2 x 2 wave grid.  Narrow outputs: 128 columns,
-  // one column tile per wave.
+  // Every load -- h from L2, W from HBM -- is an L1 miss, and each CU's capacity for pending misses
+  // bounds the streams, so wider tiles' fewer requests per MFMA pay: at 4096 @ 128256, 180 against 188 us for 128-column
+  // workgroups at 32 rows, 190 against 205 at 64, 215 against 265 at 128.  Narrow outputs: 128
+  // columns, one column tile per wave.
   const int need = (p.M + 31) / 32;
   if (!wide_columns(p.M, p.V)) {
     if (need <= 1) return launch_lm_nrt<1, 1, 1, 4, 8, 2>(p, s);
@@ -642,17 +826,25 @@ hipError_t launch_projection(const LmParams& p, hipStream_t s) {
   if (need <= 1) return launch_lm_nrt<1, 2, 1, 2, 4, 2>(p, s);
   if (need <= 2) return launch_lm_nrt<2, 2, 1, 2, 4, 2>(p, s);
   if (need <= 4) return launch_lm_nrt<4, 2, 1, 2, 4, 1>(p, s);
-  if (need >= 6 && p.ksplit == 1 && wide_rows(p.M)) {
-    // groups of 320 rows, one eight-wave workgroup per (256-column tile, group): lm_head_wide_kernel
-    LmParams q = p;
-    q.mgroups = (p.M + 319) / 320;
-    const int wgcols = (p.V + 255) / 256;
-    hipLaunchKernelGGL((lm_head_wide_kernel<5, 2, 2, 4>), dim3((unsigned)((wgcols + 7) / 8 * 8 * q.mgroups)),
-                       dim3(512), 0, s, q);
-    return hipGetLastError();
-  }
-  if (group_rows(p.M) == 192) return launch_lm_nrt<6, 2, 1, 2, 4, 1>(p, s);
-  return launch_lm_nrt<5, 2, 1, 2, 4, 1>(p, s);
+  if (p.ksplit > 1)
+    return group_rows(p.M) == 192 ? launch_lm_nrt<6, 2, 1, 2, 4, 1>(p, s) : launch_lm_nrt<5, 2, 1, 2, 4, 1>(p, s);
+  const RowGroups g = row_groups(p.M);
+  LmParams q = p;
+  q.mgroups = (p.M + g.rows - 1) / g.rows;
+  const dim3 grid((unsigned)((p.V + 255) / 256 + 7) / 8 * 8 * q.mgroups);
+  if (g.wide && g.rows == 192)
+    hipLaunchKernelGGL((lm_head_wide_kernel<3, 2, 2, 4>), grid, dim3(512), 0, s, q);
+  else if (g.wide && g.rows == 256)
+    hipLaunchKernelGGL((lm_head_wide_kernel<4, 2, 2, 4>), grid, dim3(512), 0, s, q);
+  else if (g.wide)
+    hipLaunchKernelGGL((lm_head_wide_kernel<5, 2, 2, 4>), grid, dim3(512), 0, s, q);
+  else if (q.mgroups == 1)
+    hipLaunchKernelGGL((lm_head_pair_kernel<5, true>), grid, dim3(256), 0, s, q);
+  else if (g.rows == 160)
+    hipLaunchKernelGGL((lm_head_pair_kernel<5, false>), grid, dim3(256), 0, s, q);
+  else
+    hipLaunchKernelGGL((lm_head_pair_kernel<4, false>), grid, dim3(256), 0, s, q);
+  return hipGetLastError();
 }
 
 }  // namespace spexis

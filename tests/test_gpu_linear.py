@@ -170,6 +170,8 @@ def test_pack_weight_layout(N, K):
     (64, 8224, 512, False),     # 64 x 32 tiles' last full launch is 256 column tiles: 257 take 64 x 64
     (130, 4101, 256, True),     # 64 x 64 tiles, columns not a multiple of 4, an odd count of column tiles
     (3, 40, 8448, True),        # a longer K: split over workgroups, reduced in a second launch
+    (200, 300, 8448, True),     # more rows, K in four parts of 33 steps of 64
+    (150, 33000, 512, True),    # bf16 outputs without a K split from one group of 160 rows
 ])
 def test_linear_tile_edges(rows, n_out, n_in, res):
     check(rows, n_out, n_in, res, rows * 7 + n_out)

@@ -83,6 +83,17 @@ def test_lm_head_small_shapes(rows, V, d):
     check(h, hb, w, wb, 0.8)
 
 
+# the row groups of more than 128 rows at their edges: one group of the four-wave kernel to 160, of the
+# eight-wave one to 192, 256 and 320; then groups of 128 (321, 384, 512), of 160 (385, 480) and of 320 (640)
+@pytest.mark.parametrize("rows", [129, 160, 161, 192, 193, 256, 257, 321, 384, 385, 480, 512, 640])
+def test_lm_head_row_groups(rows):
+    V, d = 1069, 512   # a last packed tile of 13 columns, workgroups whose last waves have none
+    h, hb = bf16_pair((rows, d), 21, 1.0)
+    w, wb = bf16_pair((V, d), 22, 0.05)
+    say(f"[lm head groups] rows={rows} V={V} d={d}")
+    check(h, hb, w, wb, 0.8)
+
+
 @pytest.mark.parametrize("rows", [1, 40, 64, 100])
 def test_lm_head_few_rows_wide_vocabulary(rows):
     # up to 128 rows, a vocabulary of at least 256 x 256 columns takes the 256-column
