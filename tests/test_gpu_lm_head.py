@@ -69,10 +69,9 @@ def check(h, hb, w, wb, T, rows_idx=None):
     return logits, stats
 
 
-# (320, 2048), (200, 70001), (961, 4099), (1500, 9000) and (1100, 70001) run the eight-wave
-# kernel: one group, a vocabulary whose last packed tile is part zeros, a last group of one row,
-# a last group of 220 rows with a 40-column last tile, a last group of 140 rows with a
-# part-zero last packed tile; (333, 3000) and (700, 130) the four-wave groups of 160 or 192 rows
+# (320, 2048), (200, 70001) and (1500, 9000) run the eight-wave kernel: one group of 320, one of 256 rows
+# with a vocabulary whose last packed tile is part zeros, a last group of 220 rows with a 40-column last
+# tile; (333, 3000), (700, 130), (961, 4099) and (1100, 70001) groups of 128 or 160 rows of the pair kernel
 @pytest.mark.parametrize("rows,V,d", [(1, 1000, 256), (37, 4101, 512), (320, 2048, 256), (333, 3000, 256),
                                       (700, 130, 512), (1500, 9000, 256), (200, 70001, 256), (961, 4099, 512),
                                       (1100, 70001, 512)])
