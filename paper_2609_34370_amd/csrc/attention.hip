@@ -395,6 +395,7 @@ void verify_attn_kernel(AttnParams p) {
             reinterpret_cast<u32x2*>(scr)[(col * kOc + (c ^ (col & (kOc - 1)))) * 2 + half] = w;
             __builtin_amdgcn_sched_barrier(0);   // one chunk at a time: few registers live
           }
+        wave_lds_fence();
 #pragma unroll 1
         for (int q = lane; q < 32 * kOc; q += kWave) {
           const int row = q / kOc, c = q % kOc, r = nt * 32 + row;
@@ -407,6 +408,7 @@ void verify_attn_kernel(AttnParams p) {
                                             ((int64_t)(q0 + j) * p.hq + h * p.group + gq) * D + 8 * c));
           }
         }
+        wave_lds_fence();   // the next row tile's writes, or the next item's Q, follow these reads
       } else if (starts_before) {
         if (lr < R) {
 #pragma unroll
@@ -557,11 +559,13 @@ void verify_attn_kernel(AttnParams p) {
                 u32x4{__float_as_uint(acc[nt][mt][4 * a]), __float_as_uint(acc[nt][mt][4 * a + 1]),
                       __float_as_uint(acc[nt][mt][4 * a + 2]), __float_as_uint(acc[nt][mt][4 * a + 3])};
           }
+        wave_lds_fence();
         for (int q = lane; q < 32 * kHc; q += kWave) {
           const int row = q / kHc, c = q % kHc, r = nt * 32 + row;
           const u32x4 v = scr[row * kHc + (c ^ (row & (kHc - 1)))];
           if (r < R) put4(slot1 + (int64_t)r * D + hm * (D / 2) + 4 * c, v);
         }
+        wave_lds_fence();
       }
       if (half == 0 && lr < R) {
         put1(slot1 + (int64_t)p.rmax * D + lr, m[nt]);
@@ -575,6 +579,7 @@ void verify_attn_kernel(AttnParams p) {
   // the stores drain under the last tiles' compute, it needed the loop split in two, and the
   // kernel ran slower.)
   if (stashed) {
+    wave_lds_fence();
     for (int idx = lane; idx < stash_rows * D / 4; idx += kWave)
       put4(slots + 4 * (int64_t)idx, __builtin_bit_cast(u32x4, sm_stash[wave][idx]));
 #pragma unroll

@@ -15,6 +15,15 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kWave = 64;
 
+// Orders a wave's LDS accesses where its lanes exchange values through LDS.  The hardware runs a wave's LDS
+// operations in order; the fence keeps the compiler, which sees one thread's accesses only, from moving a
+// read of another lane's value above the write, or the next write above the read.  No instruction.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
 
 // 16-byte global load / store (the address must be 16-byte aligned).

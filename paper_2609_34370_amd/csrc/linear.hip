@@ -159,12 +159,13 @@ void linear_kernel(LinearParams p) {
   for (int i = 0; i < n; i += DW) {
 #pragma unroll
     for (int jj = 0; jj < DW; ++jj) {
-      // a wave's LDS operations run in order: this step's writes follow the last step's reads
+      wave_lds_fence();   // this step's writes follow the last step's reads
 #pragma unroll
       for (int u = 0; u < kXL; ++u) {
         const int q = lane + 64 * u, r = q >> 3, kc = q & 7;
         st[r * 8 + (kc ^ ((r >> 1) & 7))] = xreg[jj % DX][u];
       }
+      wave_lds_fence();   // and its reads its writes
       load_x(xreg[jj % DX], i + jj + DX);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -186,7 +187,8 @@ void linear_kernel(LinearParams p) {
     }
   }
 
-  // the waves' partials through LDS, added in wave order
+  // the waves' partials through LDS (over the wave's own last step), added in wave order
+  wave_lds_fence();
   float* mine = reinterpret_cast<float*>(st);
 #pragma unroll
   for (int t = 0; t < RT; ++t)

@@ -189,9 +189,11 @@ __device__ __forceinline__ void row_stats_epilogue(float* stats, float* gout, fl
 #pragma clang fp contract(off)
       const int cb = n0 + 32 * (CT * wc + c);   // the tile's first column
       const bool live = cb + col < V;
+      wave_lds_fence();   // after the last tile's reads
 #pragma unroll
       for (int i = 0; i < 16; ++i)
         tile[(8 * (i >> 2) + 4 * half + (i & 3)) * kTS + col] = live ? acc[t][c][i] : -INFINITY;
+      wave_lds_fence();
       const float* mine = tile + col * kTS + 16 * half;   // 16 columns of this lane's row
       f32x4 x[4];
 #pragma unroll
