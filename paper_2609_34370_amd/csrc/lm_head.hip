@@ -789,6 +789,11 @@ static RowGroups row_groups(int64_t M) {
   return {false, p160 <= p128 ? 160 : 128};
 }
 
+// The kernels of more than 128 rows address a workgroup's rows of h (up to 320) and its packed tiles of W
+// (256 rows) by 32-bit byte offsets; a longer contraction keeps lm_head_kernel and its 64-bit addresses.
+constexpr int kMaxOffsetDim = 1 << 21;
+static_assert((int64_t)kMaxOffsetDim * 320 * 2 < (1ll << 31), "the rows of a group of 320");
+
 // Row groups of lm_head_kernel, which keeps K splits (and their odd step counts): 192 rows (six tiles) when
 // that pads M to at most 5% more rows than groups of 160 (five tiles), else 160.
 static int64_t group_rows(int64_t M) {
@@ -828,7 +833,7 @@ hipError_t launch_projection(const LmParams& p, hipStream_t s) {
   if (need <= 1) return launch_lm_nrt<1, 2, 1, 2, 4, 2>(p, s);
   if (need <= 2) return launch_lm_nrt<2, 2, 1, 2, 4, 2>(p, s);
   if (need <= 4) return launch_lm_nrt<4, 2, 1, 2, 4, 1>(p, s);
-  if (p.ksplit > 1)
+  if (p.ksplit > 1 || p.d > kMaxOffsetDim)
     return group_rows(p.M) == 192 ? launch_lm_nrt<6, 2, 1, 2, 4, 1>(p, s) : launch_lm_nrt<5, 2, 1, 2, 4, 1>(p, s);
   const RowGroups g = row_groups(p.M);
   LmParams q = p;

@@ -93,6 +93,30 @@ def test_lm_head_row_groups(rows):
     check(h, hb, w, wb, 0.8)
 
 
+@pytest.mark.parametrize("rows", [129, 161])
+def test_lm_head_contraction_past_32_bit_offsets(rows):
+    # a workgroup's packed weight (256 rows of d) and its rows of h both come to more than 2^31 bytes (the
+    # weight to more than 2^32).  h and W are zero but for 40 spread columns of small whole numbers, whose
+    # products are exact in fp32 in any order.
+    V, d = 256, (1 << 23) + 256
+    g = torch.Generator().manual_seed(rows)
+    at = torch.cat([torch.tensor([0, 63, 64, d - 65, d - 1]), torch.randint(0, d, (35,), generator=g)]).unique()
+    hv = torch.randint(-4, 5, (rows, len(at)), generator=g).float()
+    wv = torch.randint(-4, 5, (V, len(at)), generator=g).float()
+    h = torch.zeros((rows, d), dtype=torch.bfloat16, device="cuda")
+    w = torch.zeros((V, d), dtype=torch.bfloat16, device="cuda")
+    h[:, at.cuda()] = hv.to(torch.bfloat16).cuda()
+    w[:, at.cuda()] = wv.to(torch.bfloat16).cuda()
+    say(f"[lm head long contraction] rows={rows} d={d}")
+    packed = sx.spexis_pack_weight(w)
+    del w
+    logits = torch.empty((rows, V), device="cuda")
+    stats = torch.empty((rows, sx.spexis_lm_head_tiles(V), 2), device="cuda")
+    sx.spexis_lm_head(h, packed, stats, logits=logits, temperature=1.0)
+    torch.cuda.synchronize()
+    assert torch.equal(logits.cpu(), hv @ wv.T)
+
+
 @pytest.mark.parametrize("rows", [1, 40, 64, 100])
 def test_lm_head_few_rows_wide_vocabulary(rows):
     # up to 128 rows, a vocabulary of at least 256 x 256 columns takes the 256-column
