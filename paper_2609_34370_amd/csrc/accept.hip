@@ -67,6 +67,14 @@ struct Geom {
   int t0, d0, k, valid;
 };
 
+// Launches of a workgroup of up to 1024 threads per sequence: x times its threads must stay below 2^32, so
+// more than kSeqGrid sequences take rows of the grid.
+constexpr int kSeqGrid = 1 << 21;
+static dim3 seq_grid(int B) {
+  return dim3((unsigned)(B < kSeqGrid ? B : kSeqGrid), (unsigned)(((int64_t)B + kSeqGrid - 1) / kSeqGrid));
+}
+__device__ __forceinline__ int block_seq() { return (int)(blockIdx.y * kSeqGrid + blockIdx.x); }
+
 __device__ __forceinline__ Geom load_geom(const AcceptParams& p, int b) {
   const u32x4 v = *reinterpret_cast<const u32x4*>(p.geo + 4 * (int64_t)b);
   return Geom{(int)v[0], (int)v[1], (int)v[2], (int)v[3]};
@@ -660,7 +668,8 @@ constexpr int kGivenThreads = 1024;
 __global__ __launch_bounds__(kGivenThreads) void accept_given_kernel(AcceptParams p) {
   constexpr int kGivenWaves = kGivenThreads / kWave;
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  const int b = blockIdx.x;
+  const int b = block_seq();
+  if (b >= p.B) return;
   int n;
   const Geom g = seq_geom(p, b, n);
   const bool tests = wave == 0 && lane < g.k;   // k <= kAcceptMaxK < kWave
@@ -1152,7 +1161,8 @@ template <int TH, int F4, bool kVec>
 __global__ __launch_bounds__(TH) void accept_probs_kernel(AcceptParams p) {
   constexpr int NW = TH / kWave, NE = 4 * F4;
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  const int b = blockIdx.x;
+  const int b = block_seq();
+  if (b >= p.B) return;
   int n;
   const Geom g = seq_geom(p, b, n);
   TestIn t;
@@ -1213,7 +1223,8 @@ template <bool kVec>
 __global__ __launch_bounds__(kShortThreads) void accept_short_kernel(AcceptParams p) {
   constexpr int NW = kShortThreads / kWave, kLoads = kShortRow / (4 * kWave);
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  const int b = blockIdx.x;
+  const int b = block_seq();
+  if (b >= p.B) return;
   int n;
   const Geom g = seq_geom(p, b, n);
   TestIn t;
@@ -1286,13 +1297,13 @@ __global__ __launch_bounds__(kShortThreads) void accept_short_kernel(AcceptParam
 template <bool kVec>
 static hipError_t launch_one_kernel(const AcceptParams& p, hipStream_t s) {
   if (p.kind == 1)
-    hipLaunchKernelGGL((accept_short_kernel<kVec>), dim3(p.B), dim3(kShortThreads), 0, s, p);
+    hipLaunchKernelGGL((accept_short_kernel<kVec>), seq_grid(p.B), dim3(kShortThreads), 0, s, p);
   else if (p.V <= 4 * 256 * 4)
-    hipLaunchKernelGGL((accept_probs_kernel<256, 4, kVec>), dim3(p.B), dim3(256), 0, s, p);
+    hipLaunchKernelGGL((accept_probs_kernel<256, 4, kVec>), seq_grid(p.B), dim3(256), 0, s, p);
   else if (p.V <= 4 * 1024 * 4)
-    hipLaunchKernelGGL((accept_probs_kernel<1024, 4, kVec>), dim3(p.B), dim3(1024), 0, s, p);
+    hipLaunchKernelGGL((accept_probs_kernel<1024, 4, kVec>), seq_grid(p.B), dim3(1024), 0, s, p);
   else
-    hipLaunchKernelGGL((accept_probs_kernel<1024, 8, kVec>), dim3(p.B), dim3(1024), 0, s, p);
+    hipLaunchKernelGGL((accept_probs_kernel<1024, 8, kVec>), seq_grid(p.B), dim3(1024), 0, s, p);
   return hipGetLastError();
 }
 
@@ -1476,8 +1487,14 @@ __global__ __launch_bounds__(TH) void softmax_chunk_kernel(const float* logits, 
 
 template <int TH, int F4, bool kTail>
 static hipError_t launch_softmax_rows(const float* logits, float* probs, int64_t rows, int V, float c, hipStream_t s) {
-  hipLaunchKernelGGL((softmax_rows_kernel<TH, F4, kTail>), dim3((unsigned)rows), dim3(TH), 0, s, logits, probs, V, c);
-  return hipGetLastError();
+  constexpr int64_t kMost = (1ll << 32) / TH - 1;   // a launch's threads stay below 2^32
+  for (int64_t r0 = 0; r0 < rows; r0 += kMost) {
+    hipLaunchKernelGGL((softmax_rows_kernel<TH, F4, kTail>), dim3((unsigned)(rows - r0 < kMost ? rows - r0 : kMost)),
+                       dim3(TH), 0, s, logits + r0 * V, probs + r0 * V, V, c);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 constexpr int kSoftmaxChunk = 4096;   // entries of a chunk, at most (256 threads of 16)
@@ -1561,7 +1578,7 @@ hipError_t launch_accept(const AcceptParams& p, hipStream_t s) {
     return vec ? launch_one_kernel<true>(p, s) : launch_one_kernel<false>(p, s);
   if (p.kind == 1 && p.ext_tstats) {
     // Statistics given: every test in one launch, then the sampled rows.
-    hipLaunchKernelGGL(accept_given_kernel, dim3(p.B), dim3(kGivenThreads), 0, s, p);
+    hipLaunchKernelGGL(accept_given_kernel, seq_grid(p.B), dim3(kGivenThreads), 0, s, p);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(accept_stream_kernel, dim3(items), dim3(kThreads), 0, s, p, 0);
     if ((e = hipGetLastError()) != hipSuccess) return e;

@@ -856,3 +856,50 @@ def test_softmax_row_length_edges(rows, V):
         assert abs(got.double()[ok].sum(1) - 1).max() <= 1e-5
         for r in bad:
             assert torch.isnan(got[r]).all()
+
+
+# ------------------------------------------- more rows than one launch of 1024-thread workgroups holds
+
+@pytest.mark.parametrize("form", ["probs", "logits", "given statistics"])
+def test_sample_more_rows_than_one_grid_dimension(form):
+    # 2^22 workgroups of 1024 threads are 2^32 threads: a launch of them in one grid dimension ran only what is
+    # left modulo 2^32, without an error.  A row's only token is
+    # its number modulo V
+    rows, V = (1 << 22) + 3, 3
+    free = torch.cuda.mem_get_info()[0]
+    if free < 4 << 30:
+        pytest.skip(f"{free >> 20} MiB free")
+    want = (torch.arange(rows, device="cuda") % V).to(torch.int32)
+    x = torch.zeros((rows, V), device="cuda").scatter_(1, want.long().unsqueeze(1), 1.0)
+    kind, stats = sx.SPEXIS_INPUT_PROBS, None
+    if form != "probs":
+        kind, x = sx.SPEXIS_INPUT_LOGITS, x.log_()
+    if form == "given statistics":
+        stats = torch.tensor([0.0, 1.0], device="cuda").repeat(rows, 1).view(rows, 1, 2)
+    u = torch.rand(rows, device="cuda")
+    tok, status = (torch.full((rows,), 77, dtype=torch.int32, device="cuda") for _ in range(2))
+    ws = torch.empty(sx.spexis_sample_workspace_size(rows, V), dtype=torch.uint8, device="cuda")
+    say(f"[sample rows] {form}: {rows} rows")
+    sx.spexis_sample_tokens(kind, x, u, tok, status, ws, stats=stats)
+    torch.cuda.synchronize()
+    assert (status == 0).all() and torch.equal(tok, want)
+
+
+def test_softmax_more_rows_than_one_launch():
+    # 2^22 rows of a length whose workgroups have 1024 threads: 69 GB, in place
+    rows, V = (1 << 22) + 3, 4100
+    free = torch.cuda.mem_get_info()[0]
+    if free < 80 << 30:
+        pytest.skip(f"{free >> 20} MiB free")
+    x = torch.empty((rows, V), device="cuda")
+    row = torch.linspace(-6.0, 2.0, V, device="cuda")
+    x[:] = row
+    say(f"[softmax rows] {rows} rows of {V}")
+    sx.spexis_softmax_rows(x, x, 1.0)
+    torch.cuda.synchronize()
+    want = torch.softmax(row.double(), 0)
+    assert (x[0].double() - want).abs().max() <= 1e-5 * want.max()
+    for r in range(0, rows, 1 << 19):
+        assert bool((x[r: r + (1 << 19)] == x[0]).all()), r
+    del x
+    torch.cuda.empty_cache()
