@@ -218,7 +218,8 @@ int spexis_verify_attention(const void* k_cache, const void* v_cache, int32_t nu
   p.hq = num_q_heads;
   p.group = group;
   p.rmax = group * max_query_len;
-  p.tiles_per_wave = tpw;
+  p.least = kv_chunk_tokens > 0 ? spexis::AttnLeast{tpw, INT32_MAX, 0, INT32_MAX, INT32_MAX}
+                                : spexis::attn_least(num_seqs, num_kv_heads, head_dim, p.rmax);
   p.nshares = nshares;
   p.nwaves = nwaves;
   p.skew = skew;

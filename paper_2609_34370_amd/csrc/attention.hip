@@ -113,15 +113,9 @@ __device__ __forceinline__ void advance(const AttnParams& p, Cursor& c) {
 // Share geometry of a head's tile stream: shares pair up, shares 2j and 2j+1 covering tiles
 // [2jP, 2(j+1)P), the first (the wave on an even XCD) P + dlt of them and the second P - dlt.
 // dlt = 0 gives equal shares of P.
-// P of a head's `total` tiles: an even split over its shares, but at least kAttnMinTilesPerWave tiles
-// each, and more when a head has many (total / 64, up to kAttnMinTilesLong): a share's start and its
-// partial, written and merged, cost about as much as those tiles (the call at one sequence of 16384
-// keys and 8 KV heads, 512 tiles a head: 25.8 us with shares of 6, 27.0 of 5, 30.3 of 4, 25.9 of 8;
-// at 128 tiles 17.1 us with shares of 2, 17.5 of 4, 18.5 of 6).
+// P of a head's `total` tiles: an even split over its shares, but at least attn_least_tiles each.
 __device__ __forceinline__ int share_tiles(const AttnParams& p, int total) {
-  const int least = p.tiles_per_wave > 0 ? p.tiles_per_wave
-                                         : clampi(total / 64, kAttnMinTilesPerWave, kAttnMinTilesLong);
-  return max(least, (total + p.nshares - 1) / p.nshares);
+  return max(attn_least_tiles(p.least, total), (total + p.nshares - 1) / p.nshares);
 }
 __device__ __forceinline__ int share_delta(int P, int skew) { return (int)(((int64_t)P * skew) >> 10); }
 __device__ __forceinline__ int64_t share_first(int s, int P, int dlt) {
@@ -169,14 +163,14 @@ void verify_attn_kernel(AttnParams p) {
   if (share >= p.nshares) return no_share();
 
   // ---- this wave's share [g0, g0 + cnt) of head h's tile stream
-  int total, b0 = 0, f0 = 0;
+  int total, P, b0 = 0, f0 = 0;   // P: the tiles of a share
   Cursor start;
   if (p.num_seqs <= kWave) {
     // one pass: lane b holds sequence b's geometry; the share start is read from the lanes
     const SeqGeo gl = lane < p.num_seqs ? seq_geo(p, p.qsl, p.seq_lens, lane) : SeqGeo{0, 0, 0, 0};
     const int incl = wave_incl_scan_i32(gl.nt, lane);
     total = __builtin_amdgcn_readlane(incl, kWave - 1);   // < 2^31 (host)
-    const int P = share_tiles(p, total);
+    P = share_tiles(p, total);
     if (share_first(share, P, share_delta(P, p.skew)) >= total) return no_share();
     const int g0 = (int)share_first(share, P, share_delta(P, p.skew));
     const uint64_t hit = __builtin_amdgcn_ballot_w64(incl > g0);
@@ -193,7 +187,7 @@ void verify_attn_kernel(AttnParams p) {
     for (int base = 0; base < p.num_seqs; base += kWave)
       if (base + lane < p.num_seqs) per_lane += seq_geo(p, p.qsl, p.seq_lens, base + lane).nt;
     total = __builtin_amdgcn_readfirstlane(wave_sum_i32(per_lane));   // < 2^31 (host)
-    const int P = share_tiles(p, total);
+    P = share_tiles(p, total);
     if (share_first(share, P, share_delta(P, p.skew)) >= total) return no_share();
     const int g0 = (int)share_first(share, P, share_delta(P, p.skew));
     // the sequence holding tile g0, and the stream index of its first tile
@@ -220,7 +214,6 @@ void verify_attn_kernel(AttnParams p) {
     start.S = g.S;
     start.t = g0 - f0;
   }
-  const int P = share_tiles(p, total);
   const int dlt = share_delta(P, p.skew);
   const int g0 = (int)share_first(share, P, dlt);
   const int cnt = min(share_size(share, P, dlt), total - g0);

@@ -17,6 +17,54 @@ struct AppendParams {
   int num_blocks, hkv, block_size, head_dim, num_seqs, max_blocks, total_tokens;
 };
 
+constexpr int kAttnHdrInts = 8;           // per-wave header of the partial an item's first wave leaves
+constexpr int kAttnMinTilesPerWave = 2;   // floor of the even split (short batches)
+constexpr int kAttnMaxWaves = 1024;       // waves of the even split: one per SIMD of 256 CUs
+// The fewest tiles a share of the even split takes, for a head's `total` tiles over num_seqs sequences of R
+// rows at most (per KV head).  A share's start and its partial, written and merged, cost about as much as a few
+// tiles, and a sequence that a share holds whole has no partial; but a longer share is a longer chain.
+//   * Where shares of two tiles leave waves idle (fewer than 2 kAttnMaxWaves tiles over all heads) the chain
+//     counts: 128-wide heads, 20 rows, one KV head: 15.9 us with shares of 2 and 21.1 of 6 at 64 sequences of
+//     256 keys, 19.0 and 21.7 at 16 of 1024.  Not so where each sequence is cut into hundreds of shares, whose
+//     merge is the longer chain: a sequence of 32768 keys takes 35.9 us with shares of 2, 28.7 of 4, 26.2 of 6
+//     (from 512 tiles a sequence 4, with more than 32 rows, whose partials are larger, from 256; from 1024, 6).
+//     Sequences of three or four tiles go whole to one share, with up to 32 rows once half the waves are
+//     busy: 0.60 to 0.71 of the time with shares of 2 at 63 rows, 0.81 to 0.86 at 20, 0.97 to 0.99 at 8.
+//   * Above that the partials count: shares of 4 take 0.68 to 0.92 of the time of shares of 2 (0.52 to 0.92 at
+//     63 rows), but for sequences of one or two tiles, of which each share of 4 would hold several (1.06 to
+//     1.20).  With twice the tiles, shares of 6 take 0.80 to 0.94 of the time of shares of 4 for up to 32 rows
+//     of 128-wide heads; sequences of fewer than eight tiles lose (1.07 to 1.24), as do 64-wide heads, whose
+//     tiles are half as long (1.00 to 1.08), and more rows (up to 1.13).  A single sequence takes shares of 6
+//     in either case (0.95 to 0.98 of the time with 4).
+// The kernel only compares `total` with limits the host works out.
+struct AttnLeast {
+  int tiles;        // the fewest, but
+  int lo4, hi4;     // 4 for lo4 <= total < hi4
+  int from4, from6; // and from these totals on 4, resp. 6
+};
+inline AttnLeast attn_least(int64_t num_seqs, int64_t hkv, int head_dim, int R) {
+  const auto at_least = [](int64_t a, int64_t b) { return a > b ? a : b; };
+  const auto limit = [](int64_t a, int64_t b) { return (int)(a < b ? a : b); };
+  constexpr int64_t kNever = INT32_MAX;   // `total` stays below 2^31
+  const auto busy = [&](int64_t all) { return (all + hkv - 1) / hkv; };   // a head's share of `all` tiles
+  const int64_t full = at_least(busy(2 * kAttnMaxWaves), 3 * num_seqs);
+  const int64_t twice = head_dim == 128 && R <= 32 ? at_least(busy(4 * kAttnMaxWaves), 8 * num_seqs) : kNever;
+  AttnLeast l;
+  l.tiles = kAttnMinTilesPerWave;
+  l.lo4 = R < 8 ? (int)kNever : limit(at_least(R > 32 ? 0 : busy(kAttnMaxWaves), 3 * num_seqs), kNever);
+  l.hi4 = limit(5 * num_seqs, full);
+  const int64_t cut = (R > 32 ? 256 : 512) * num_seqs;
+  l.from4 = limit(cut < full ? cut : full, kNever);
+  l.from6 = limit(1024 * num_seqs < twice ? 1024 * num_seqs : twice, num_seqs == 1 ? full : kNever);
+  return l;
+}
+__host__ __device__ inline int attn_least_tiles(const AttnLeast& l, int total) {
+  return total >= l.from6 ? 6 : total >= l.from4 || (total >= l.lo4 && total < l.hi4) ? 4 : l.tiles;
+}
+// Tiles moved, per 1024, from the share of each pair on an odd XCD to the one on an even XCD:
+// waves on odd XCDs stream the cache a few per cent slower.
+constexpr int kAttnXcdSkew = 28;
+
 struct AttnParams {
   const void* k_cache;
   const void* v_cache;
@@ -29,20 +77,12 @@ struct AttnParams {
   int num_blocks, hkv, block_size, head_dim, num_seqs, max_blocks, total_tokens;
   int hq, group;         // Hq, G = Hq / Hkv
   int rmax;              // G * max_query_len (rows per (sequence, KV head)), <= 64
-  int tiles_per_wave;    // 32-key tiles per share; 0: the even split of each head's tiles
+  AttnLeast least;       // the fewest 32-key tiles per share
   int nshares;           // shares per KV head; wave s*hkv + h takes share s of head h
   int nwaves;            // waves of the attention grid (4 per workgroup, >= nshares * hkv)
   int skew;              // 0: equal shares; else paired shares, the even-XCD one skew/1024 longer
   float scale_log2e;     // scale * log2(e): scores live in the base-2 domain
 };
-
-constexpr int kAttnHdrInts = 8;           // per-wave header of the partial an item's first wave leaves
-constexpr int kAttnMinTilesPerWave = 2;   // floor of the even split (short batches)
-constexpr int kAttnMinTilesLong = 6;      // and of a head with many tiles over few sequences
-constexpr int kAttnMaxWaves = 1024;       // waves of the even split: one per SIMD of 256 CUs
-// Tiles moved, per 1024, from the share of each pair on an odd XCD to the one on an even XCD:
-// waves on odd XCDs stream the cache a few per cent slower.
-constexpr int kAttnXcdSkew = 28;
 
 // One partial slot: [rmax][D] unnormalised output, then rmax reference maxima and rmax sums.
 // Rounded up to 16 floats so that every slot starts 64-byte aligned.
