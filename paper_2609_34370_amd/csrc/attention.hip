@@ -766,8 +766,10 @@ static hipError_t launch_attn_t(const AttnParams& p, hipStream_t s) {
   // Few, long items: at least kMergeWideShares shares per sequence (the call, wide merge against
   // attn_merge_kernel: 30.3 against 60.7 us at one sequence of 16384 keys, 25.7 against 30.8 at 4 of
   // 1000-4096, 30.2 against 32.0 at 8 of them, where there are 16 shares a sequence; 45.4 against 43.0
-  // at 16 of them).
-  if (p.nshares >= kMergeWideShares * p.num_seqs) {
+  // at 16 of them).  At just that many, items of up to 8 rows of 64 take attn_merge_kernel as few round
+  // trips, without the combination through LDS (12.2 against 12.9 us at one sequence of 1024 keys).
+  const bool small = D == 64 && p.rmax <= 8;
+  if (p.nshares / (kMergeWideShares + (small ? 1 : 0)) >= p.num_seqs) {
     const int rg = (p.rmax + kMergeRows - 1) / kMergeRows;
     hipLaunchKernelGGL((attn_merge_wide_kernel<D>), dim3((unsigned)(p.num_seqs * p.hkv * rg)), dim3(512), 0, s, p, rg);
     return hipGetLastError();

@@ -1,0 +1,53 @@
+"""Which kernels a call launches, at sizes where another choice is slower (torch's profiler lists them)."""
+import sys
+
+import pytest
+import torch
+from torch.profiler import ProfilerActivity, profile
+
+from paper_2609_34370_amd import spexis as sx
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print(*a, file=sys.stderr, flush=True)
+
+
+def launched(call) -> list:
+    """Names of this library's kernels that call() launches, without their arguments."""
+    call()   # the first call loads the kernels
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    names = [e.name for e in p.events() if "spexis::" in e.name]
+    return [n[n.index("spexis::") + len("spexis::"):].split("(")[0] for n in names]
+
+
+def zeros(*shape):
+    return torch.zeros(shape, dtype=torch.int32, device="cuda")
+
+
+@pytest.mark.parametrize("batch,ctx,group,dim,merge", [
+    (1, 1024, 8, 64, "attn_merge_kernel"),         # 16 shares of a sequence, 8 rows of 64
+    (1, 1024, 9, 64, "attn_merge_wide_kernel"),
+    (1, 1024, 8, 128, "attn_merge_wide_kernel"),
+    (1, 2048, 8, 64, "attn_merge_wide_kernel"),
+    (64, 1024, 8, 128, "attn_merge_kernel"),
+])
+def test_attention_merge(batch, ctx, group, dim, merge):
+    hkv, bs = 2, 32
+    nb = ctx // bs
+    pool = torch.zeros(batch * nb * hkv * bs * dim, dtype=torch.bfloat16, device="cuda")
+    q = torch.zeros((batch, hkv * group, dim), dtype=torch.bfloat16, device="cuda")
+    out = torch.empty_like(q)
+    qsl = torch.arange(batch + 1, dtype=torch.int32, device="cuda")
+    lens = torch.full((batch,), ctx, dtype=torch.int32, device="cuda")
+    tables = torch.arange(batch * nb, dtype=torch.int32, device="cuda").view(batch, nb)
+    ws = torch.empty(sx.spexis_verify_attention_workspace_size(batch, hkv * group, hkv, dim, 1, ctx), dtype=torch.uint8,
+                     device="cuda")
+    got = launched(lambda: sx.spexis_verify_attention(pool, pool, batch * nb, hkv, bs, dim, qsl, lens, tables, batch, 1,
+                                                      ctx, q, hkv * group, dim ** -0.5, out, ws))
+    say(f"[merge] {batch} x {ctx}, {group} rows of {dim}: {got}")
+    assert [n.split("<")[0] for n in got] == ["verify_attn_kernel", merge]
