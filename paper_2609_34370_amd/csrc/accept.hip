@@ -67,8 +67,9 @@ struct Geom {
   int t0, d0, k, valid;
 };
 
-// Launches of a workgroup of up to 1024 threads per sequence: x times its threads must stay below 2^32, so
-// more than kSeqGrid sequences take rows of the grid.
+// A launch of a workgroup of 1024 threads per sequence: their number must stay below 2^32 in a dimension of the
+// grid, so more than kSeqGrid sequences take rows of it.  (The kernels of short rows don't: it cost
+// accept_short_kernel<false> 0.5 to 1.5 us at any size.  That many sequences take the other launches.)
 constexpr int kSeqGrid = 1 << 21;
 static dim3 seq_grid(int B) {
   return dim3((unsigned)(B < kSeqGrid ? B : kSeqGrid), (unsigned)(((int64_t)B + kSeqGrid - 1) / kSeqGrid));
@@ -1161,8 +1162,7 @@ template <int TH, int F4, bool kVec>
 __global__ __launch_bounds__(TH) void accept_probs_kernel(AcceptParams p) {
   constexpr int NW = TH / kWave, NE = 4 * F4;
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  const int b = block_seq();
-  if (b >= p.B) return;
+  const int b = blockIdx.x;
   int n;
   const Geom g = seq_geom(p, b, n);
   TestIn t;
@@ -1223,8 +1223,7 @@ template <bool kVec>
 __global__ __launch_bounds__(kShortThreads) void accept_short_kernel(AcceptParams p) {
   constexpr int NW = kShortThreads / kWave, kLoads = kShortRow / (4 * kWave);
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  const int b = block_seq();
-  if (b >= p.B) return;
+  const int b = blockIdx.x;
   int n;
   const Geom g = seq_geom(p, b, n);
   TestIn t;
@@ -1297,13 +1296,13 @@ __global__ __launch_bounds__(kShortThreads) void accept_short_kernel(AcceptParam
 template <bool kVec>
 static hipError_t launch_one_kernel(const AcceptParams& p, hipStream_t s) {
   if (p.kind == 1)
-    hipLaunchKernelGGL((accept_short_kernel<kVec>), seq_grid(p.B), dim3(kShortThreads), 0, s, p);
+    hipLaunchKernelGGL((accept_short_kernel<kVec>), dim3(p.B), dim3(kShortThreads), 0, s, p);
   else if (p.V <= 4 * 256 * 4)
-    hipLaunchKernelGGL((accept_probs_kernel<256, 4, kVec>), seq_grid(p.B), dim3(256), 0, s, p);
+    hipLaunchKernelGGL((accept_probs_kernel<256, 4, kVec>), dim3(p.B), dim3(256), 0, s, p);
   else if (p.V <= 4 * 1024 * 4)
-    hipLaunchKernelGGL((accept_probs_kernel<1024, 4, kVec>), seq_grid(p.B), dim3(1024), 0, s, p);
+    hipLaunchKernelGGL((accept_probs_kernel<1024, 4, kVec>), dim3(p.B), dim3(1024), 0, s, p);
   else
-    hipLaunchKernelGGL((accept_probs_kernel<1024, 8, kVec>), seq_grid(p.B), dim3(1024), 0, s, p);
+    hipLaunchKernelGGL((accept_probs_kernel<1024, 8, kVec>), dim3(p.B), dim3(1024), 0, s, p);
   return hipGetLastError();
 }
 
@@ -1574,7 +1573,8 @@ hipError_t launch_accept(const AcceptParams& p, hipStream_t s) {
   // sequences are better spread over the chip: 29.3 against 24.8 us at 16 sequences of 31999, 32.0
   // against 38.4 at 128.
   const bool vec = (p.V & 3) == 0;
-  if (p.kind == 1 ? !p.ext_tstats && p.V <= kShortRow : p.V <= kProbsRow && (vec || p.V <= 16384 || p.B >= 64))
+  if (p.B <= kSeqGrid &&
+      (p.kind == 1 ? !p.ext_tstats && p.V <= kShortRow : p.V <= kProbsRow && (vec || p.V <= 16384 || p.B >= 64)))
     return vec ? launch_one_kernel<true>(p, s) : launch_one_kernel<false>(p, s);
   if (p.kind == 1 && p.ext_tstats) {
     // Statistics given: every test in one launch, then the sampled rows.
