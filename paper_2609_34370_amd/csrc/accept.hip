@@ -1562,19 +1562,36 @@ static hipError_t launch_search(const AcceptParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Logit rows for accept_short_kernel, which reads the 2k + 1 rows of every sequence whatever the tests decide:
+// at most kShortRow entries, kShortBytes in all (then rounds, which leave the rows past a rejection unread: 151
+// against 191 us at 1024 sequences of 32 drafts, 4096 entries), and no chain of loads in a wave that outlasts
+// the rounds' launches, which take longer the more sequences there are.  At 1, 128 and 512 sequences of 8
+// drafts, 10.2, 10.0 and 16.5 against 17.2, 25.0 and 40.7 us with 1000 entries, 10.6, 11.8 and 33.3 against
+// 19.1, 25.5 and 47.2 us with 4096; but with 32 drafts 22.5 against 19.4 us at one sequence of 4096 (80 loads
+// a wave) and 23.3 against 26.5 at 16, and of 4095, a load an entry, 67.5 against 24.5 us at one sequence (320
+// loads), 70.5 against 65.7 at 128 and 71.5 against 100.7 at 256.  Without drafts there is one round, whose
+// workgroups are four to a CU where these (all registers of a CU, at such lengths) are one: 30.4 against 24.9
+// us at 1024 rows of 999 entries, 16.7 against 19.8 at 512.
+constexpr int64_t kShortBytes = 400ll << 20;
+static bool short_logits(const AcceptParams& p) {
+  const int64_t rows = 2 * (int64_t)p.max_k + 1, waves = kShortThreads / kWave;
+  const int64_t entries = (p.V & 3) == 0 ? 4 * kWave : kWave;   // of one load of a wave
+  const int64_t loads = (rows + waves - 1) / waves * ((p.V + entries - 1) / entries);
+  return p.V <= kShortRow && loads <= 64 + (int64_t)p.B && p.B * rows * p.V * 4 <= kShortBytes &&
+         ((p.V & 3) == 0 || p.max_k > 0 || p.B <= 512);
+}
+
 hipError_t launch_accept(const AcceptParams& p, hipStream_t s) {
   const unsigned items = (unsigned)((int64_t)p.B * p.nsub);
   hipError_t e;
-  // Short rows: one launch, a workgroup per sequence.  Measured against the launches below: logits at
-  // 1, 128 and 512 sequences of 8 drafts, 10.2, 10.0 and 16.5 against 17.2, 25.0 and 40.7 us with 1000
-  // entries, 10.6, 11.8 and 33.3 against 19.1, 25.5 and 47.2 us with 4096; probabilities (k = 4) 10
-  // against 19 to 25 us up to 4096 entries, 16.4, 20.9 and 51.0 against 19.2, 29.3 and 67.3 us with
-  // 32000.  Rows of more than 16384 entries that are not a multiple of 4 (four loads for one) at few
+  // Short rows: one launch, a workgroup per sequence.  Measured against the launches below: probabilities
+  // (k = 4) 10 against 19 to 25 us up to 4096 entries, 16.4, 20.9 and 51.0 against 19.2, 29.3 and 67.3 us
+  // with 32000.  Rows of more than 16384 entries that are not a multiple of 4 (four loads for one) at few
   // sequences are better spread over the chip: 29.3 against 24.8 us at 16 sequences of 31999, 32.0
   // against 38.4 at 128.
   const bool vec = (p.V & 3) == 0;
   if (p.B <= kSeqGrid &&
-      (p.kind == 1 ? !p.ext_tstats && p.V <= kShortRow : p.V <= kProbsRow && (vec || p.V <= 16384 || p.B >= 64)))
+      (p.kind == 1 ? !p.ext_tstats && short_logits(p) : p.V <= kProbsRow && (vec || p.V <= 16384 || p.B >= 64)))
     return vec ? launch_one_kernel<true>(p, s) : launch_one_kernel<false>(p, s);
   if (p.kind == 1 && p.ext_tstats) {
     // Statistics given: every test in one launch, then the sampled rows.

@@ -51,3 +51,27 @@ def test_attention_merge(batch, ctx, group, dim, merge):
                                                       ctx, q, hkv * group, dim ** -0.5, out, ws))
     say(f"[merge] {batch} x {ctx}, {group} rows of {dim}: {got}")
     assert [n.split("<")[0] for n in got] == ["verify_attn_kernel", merge]
+
+
+def accept_kernels(kind, B, V, k):
+    T = B * (k + 1)
+    qsl = torch.arange(B + 1, dtype=torch.int32, device="cuda") * (k + 1)
+    # equal probabilities, every draft accepted
+    rows = torch.full((T, V), 1.0 / V if kind == sx.SPEXIS_INPUT_PROBS else 0.0, device="cuda")
+    u, us, ids = torch.zeros(T - B, device="cuda"), torch.full((B,), 0.5, device="cuda"), zeros(T - B)
+    ws = torch.empty(sx.spexis_accept_workspace_size(B, V, k), dtype=torch.uint8, device="cuda")
+    a, tok, status = zeros(B), zeros(B, k + 1), zeros(B)
+    got = launched(lambda: sx.spexis_accept(kind, qsl, rows, rows[: T - B], ids, u, us, k, a, tok, status, ws))
+    say(f"[accept] kind {kind}, {B} x {k} drafts of {V}: {got}")
+    assert (status == 0).all() and (a == k).all() and (tok[:, k] == V // 2).all()
+    return [n.split("<")[0] for n in got]
+
+
+@pytest.mark.parametrize("B,V,k,one", [
+    (1, 4096, 16, True), (1, 4096, 32, False), (16, 4096, 32, True), (256, 4096, 32, True), (512, 4096, 32, False),
+    (1024, 4096, 8, True), (1024, 4096, 16, False), (1, 4095, 4, True), (1, 4095, 8, False), (64, 4095, 8, True),
+    (64, 4095, 16, False), (256, 4095, 32, True), (1, 1000, 32, True), (1, 999, 32, False), (4, 4097, 2, False),
+    (1024, 999, 0, False), (512, 999, 0, True), (1024, 1000, 0, True),
+])
+def test_short_logit_rows_are_read_whole_while_they_are_few(B, V, k, one):
+    assert (accept_kernels(sx.SPEXIS_INPUT_LOGITS, B, V, k) == ["accept_short_kernel"]) == one
