@@ -1581,17 +1581,26 @@ static bool short_logits(const AcceptParams& p) {
          ((p.V & 3) == 0 || p.max_k > 0 || p.B <= 512);
 }
 
+// Probability rows for accept_probs_kernel: 10 against 19 to 25 us of the launches below up to 4096 entries at 4
+// drafts.  Past 16384 entries a row takes a workgroup long (one CU, its registers full), and the launches below
+// spread it over the chip; but they read the sampled rows twice, which costs more the more of them there are, and
+// the more drafts, the more are residuals, of two rows: of 32000 entries, 17.4 against 14.2 us at one draw (no
+// drafts), 44.6 against 39.7 at 512; 17.1 against 14.4 at one sequence of one draft, 20.7 against 24.1 at 128;
+// 18.0 against 18.0 at 16 of 4, 21.9 against 28.4 at 128.  A row whose length is not a multiple of 4 takes four
+// loads for one: 30.8 against 27.5 us at 64 sequences of 2 drafts of 31999 entries (24.6 against 27.0 of 16385),
+// 32.6 against 36.6 at 128.
+static bool short_probs(const AcceptParams& p) {
+  if (p.V <= 16384) return true;
+  const bool spread = (p.V & 3) == 0 || p.B >= (p.V <= 24576 ? 64 : 128);
+  return p.V <= kProbsRow && spread && (int64_t)p.max_k * p.B >= 128;
+}
+
 hipError_t launch_accept(const AcceptParams& p, hipStream_t s) {
   const unsigned items = (unsigned)((int64_t)p.B * p.nsub);
   hipError_t e;
-  // Short rows: one launch, a workgroup per sequence.  Measured against the launches below: probabilities
-  // (k = 4) 10 against 19 to 25 us up to 4096 entries, 16.4, 20.9 and 51.0 against 19.2, 29.3 and 67.3 us
-  // with 32000.  Rows of more than 16384 entries that are not a multiple of 4 (four loads for one) at few
-  // sequences are better spread over the chip: 29.3 against 24.8 us at 16 sequences of 31999, 32.0
-  // against 38.4 at 128.
+  // Short rows: one launch, a workgroup per sequence.
   const bool vec = (p.V & 3) == 0;
-  if (p.B <= kSeqGrid &&
-      (p.kind == 1 ? !p.ext_tstats && short_logits(p) : p.V <= kProbsRow && (vec || p.V <= 16384 || p.B >= 64)))
+  if (p.B <= kSeqGrid && (p.kind == 1 ? !p.ext_tstats && short_logits(p) : short_probs(p)))
     return vec ? launch_one_kernel<true>(p, s) : launch_one_kernel<false>(p, s);
   if (p.kind == 1 && p.ext_tstats) {
     // Statistics given: every test in one launch, then the sampled rows.

@@ -75,3 +75,12 @@ def accept_kernels(kind, B, V, k):
 ])
 def test_short_logit_rows_are_read_whole_while_they_are_few(B, V, k, one):
     assert (accept_kernels(sx.SPEXIS_INPUT_LOGITS, B, V, k) == ["accept_short_kernel"]) == one
+
+
+@pytest.mark.parametrize("B,V,k,one", [
+    (1, 16384, 0, True), (512, 16385, 0, False), (512, 32000, 0, False), (1, 32000, 1, False), (16, 32000, 4, False),
+    (16, 32000, 8, True), (64, 32000, 2, True), (128, 32000, 1, True), (64, 31999, 2, False), (128, 31999, 1, True),
+    (64, 16385, 2, True), (64, 16385, 1, False), (128, 32772, 8, False),
+])
+def test_long_probability_rows_need_many_residuals(B, V, k, one):
+    assert (accept_kernels(sx.SPEXIS_INPUT_PROBS, B, V, k) == ["accept_probs_kernel"]) == one
