@@ -1512,6 +1512,11 @@ hipError_t launch_softmax(const float* logits, float* probs, int64_t rows, int V
     hipLaunchKernelGGL((softmax_chunk_kernel<256, 4>), g, dim3(256), 0, s, logits, probs, V, chunks, c);
     return hipGetLastError();
   }
+  // Short rows hold as few entries a thread as they need: with 16 a thread at any length, 7.5 against 5.2 us at
+  // 4096 rows of 100 entries and 9.6 against 7.1 of 1000.
+  if (V <= 256) return launch_softmax_rows<64, 1, false>(logits, probs, rows, V, c, s);
+  if (V <= 1024) return launch_softmax_rows<256, 1, false>(logits, probs, rows, V, c, s);
+  if (V <= 2048) return launch_softmax_rows<256, 2, false>(logits, probs, rows, V, c, s);
   if (V <= 4096) return launch_softmax_rows<256, 4, false>(logits, probs, rows, V, c, s);
   if (V <= 16384) return launch_softmax_rows<1024, 4, false>(logits, probs, rows, V, c, s);
   if (V <= 32768) return launch_softmax_rows<1024, 8, false>(logits, probs, rows, V, c, s);

@@ -858,6 +858,11 @@ def test_softmax_row_length_edges(rows, V):
             assert torch.isnan(got[r]).all()
 
 
+@pytest.mark.parametrize("rows,V", [(5, 256), (5, 257), (5, 1024), (5, 1025), (4, 2048), (4, 2049), (5, 3), (5, 255)])
+def test_softmax_short_row_length_edges(rows, V):
+    test_softmax_row_length_edges(rows, V)
+
+
 # ------------------------------------------- more rows than one launch of 1024-thread workgroups holds
 
 @pytest.mark.parametrize("form", ["probs", "logits", "given statistics"])
