@@ -118,11 +118,23 @@ __device__ __forceinline__ void tile_of(int bid, int ntiles, int groups, int& nt
 
 // A workgroup's accumulators to memory: fp32 logits (or K-split partials) at `out` and / or bf16
 // outputs at y (+ residual), both with row stride V, from row m0 on.  One pointer per lane and
-// column tile, to which each store adds its accumulator's row offset (uniform); a group of whole
-// 32-row tiles takes no row checks.  fp32 values are written once and read by a later kernel:
-// non-temporal stores keep them from evicting the h and W lines the other workgroups still read
-// through L2 (measured at 320 x 4096 @ 128256: 469 against 480 us; at 4608 x 3584 @ 152064: 5332
-// against 5684 us).
+// column tile, which each store moves on by its accumulator's step in rows (uniform: 1, or 5 past
+// every fourth); a group of whole 32-row tiles takes no row checks.  fp32 values are written once and
+// read by a later kernel: non-temporal stores keep them from evicting the h and W lines the other
+// workgroups still read through L2 (measured at 320 x 4096 @ 128256: 469 against 480 us; at 4608 x
+// 3584 @ 152064: 5332 against 5684 us).
+template <bool kFull, int RT>
+__device__ __forceinline__ void store_column(const f32x16 (&acc)[RT], float* at, int64_t V, int left) {
+  // kept apart from the next column's checks, or the compiler holds all their masks in (spilled) registers
+  if (!kFull) asm volatile("" : "+v"(left));
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      if (kFull || 32 * t + 8 * (i >> 2) + (i & 3) < left) __builtin_nontemporal_store(acc[t][i], at);
+      at += (i & 3) == 3 ? 5 * V : V;
+    }
+}
 template <int RT, int CT, int WR, int WC>
 __device__ __forceinline__ void store_epilogue(const f32x16 (&acc)[RT][CT], float* out, uint16_t* y, const uint16_t* res,
                                                int V, int m0, int n0, int rows, int wr, int wc, int lane) {
@@ -134,14 +146,12 @@ __device__ __forceinline__ void store_epilogue(const f32x16 (&acc)[RT][CT], floa
     const int v = n0 + 32 * (CT * wc + c) + col;
     if (v >= V) continue;
     if (out) {
+      f32x16 col_acc[RT];
+#pragma unroll
+      for (int t = 0; t < RT; ++t) col_acc[t] = acc[t][c];
       float* at = out + (int64_t)(m0 + r0) * V + v;
-#pragma unroll
-      for (int t = 0; t < RT; ++t)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int dr = 32 * t + 8 * (i >> 2) + (i & 3);
-          if (full || r0 + dr < rows) __builtin_nontemporal_store(acc[t][c][i], at + (int64_t)dr * V);
-        }
+      if (full) store_column<true>(col_acc, at, V, 0);
+      else store_column<false>(col_acc, at, V, rows - r0);
     }
     if (y) {
 #pragma unroll
