@@ -779,6 +779,9 @@ static hipError_t launch_lm_nrt(const LmParams& q, hipStream_t s) {
 // twice as many workgroups the K split then fills the chip with.
 static bool wide_columns(int64_t M, int64_t N) { return M > 128 || (N + 255) / 256 >= 256; }
 
+// Workgroups of a launch, with the absent ones that round the column tiles up to the 8 XCDs.
+static int64_t launched_workgroups(int64_t N, int64_t groups) { return ((N + 255) / 256 + 7) / 8 * 8 * groups; }
+
 // More than 128 rows: the kernel and the rows of its groups.  129 to 160 rows are one group of
 // lm_head_pair_kernel, 161 to 320 one of lm_head_wide_kernel with the smallest of three heights that holds
 // them (at 4096 @ 128256, against groups of 160 of lm_head_kernel, resp. one of 320: 199 against 228 us at
@@ -786,17 +789,24 @@ static bool wide_columns(int64_t M, int64_t N) { return M > 128 || (N + 255) / 2
 // group's measured time times the groups: 100 for 320 rows of the wide kernel, 51 and 42 for 160 and 128
 // of the pair kernel (against lm_head_kernel or groups of 320: 395 against 464 us at 384 rows, 462 against
 // 574 at 480, 507 against 561 at 512, 1018 against 1143 at 1024 x 3584 @ 152064, 4240 against 4303 at 4608
-// rows there; 640 rows keep 320: 596, with 160 610; 352 rows @ 32000 are level, 104).
+// rows there; 640 rows keep 320: 596, with 160 610).  Those are vocabularies whose columns alone fill the
+// chip many times over; with few columns the rounds of workgroups over the CUs count (here and in
+// one_round_of_rows).
 struct RowGroups {
   bool wide;
   int rows;
 };
-static RowGroups row_groups(int64_t M) {
+static RowGroups row_groups(int64_t M, int64_t N) {
   if (M <= 160) return {false, 160};
   if (M <= 320) return {true, M <= 192 ? 192 : M <= 256 ? 256 : 320};
   const int64_t w320 = (M + 319) / 320 * 100, p160 = (M + 159) / 160 * 51, p128 = (M + 127) / 128 * 42;
+  const int64_t pair = p160 <= p128 ? 160 : 128;
   if (w320 <= p160 && w320 <= p128) return {true, 320};
-  return {false, p160 <= p128 ? 160 : 128};
+  // one round of the wide kernel (a workgroup a CU) against two of the pair kernel (two a CU): 120 against
+  // 134 us at 832 x 3584 @ 20000
+  if (launched_workgroups(N, (M + 319) / 320) <= 256 && launched_workgroups(N, (M + pair - 1) / pair) > 512)
+    return {true, 320};
+  return {false, (int)pair};
 }
 
 // The kernels of more than 128 rows address a workgroup's rows of h (up to 320) and its packed tiles of W
@@ -809,6 +819,15 @@ static_assert((int64_t)kMaxOffsetDim * 320 * 2 < (1ll << 31), "the rows of a gro
 static int64_t group_rows(int64_t M) {
   const int64_t p160 = (M + 159) / 160 * 160, p192 = (M + 191) / 192 * 192;
   return p192 * 20 <= p160 * 21 ? 192 : 160;
+}
+
+// Few columns, where lm_head_kernel's groups are one workgroup for each CU and the pair kernel's are not two:
+// some CUs then run two of its workgroups and the others wait (100 against 113 us at 352 x 3584 @ 32000, 95
+// against 102 at 768 @ 16000; with two for each CU the pair kernel wins: 118 against 143 us at 480 @ 32000).
+static bool one_round_of_rows(int64_t M, int64_t N) {
+  const RowGroups g = row_groups(M, N);
+  if (g.wide || M <= 160 || launched_workgroups(N, (M + g.rows - 1) / g.rows) <= 256) return false;
+  return launched_workgroups(N, (M + group_rows(M) - 1) / group_rows(M)) <= 256;
 }
 
 // The groups that a K split is sized by (one of 320 rows where those pad M little).
@@ -843,9 +862,9 @@ hipError_t launch_projection(const LmParams& p, hipStream_t s) {
   if (need <= 1) return launch_lm_nrt<1, 2, 1, 2, 4, 2>(p, s);
   if (need <= 2) return launch_lm_nrt<2, 2, 1, 2, 4, 2>(p, s);
   if (need <= 4) return launch_lm_nrt<4, 2, 1, 2, 4, 1>(p, s);
-  if (p.ksplit > 1 || p.d > kMaxOffsetDim)
+  if (p.ksplit > 1 || p.d > kMaxOffsetDim || one_round_of_rows(p.M, p.V))
     return group_rows(p.M) == 192 ? launch_lm_nrt<6, 2, 1, 2, 4, 1>(p, s) : launch_lm_nrt<5, 2, 1, 2, 4, 1>(p, s);
-  const RowGroups g = row_groups(p.M);
+  const RowGroups g = row_groups(p.M, p.V);
   LmParams q = p;
   q.mgroups = (p.M + g.rows - 1) / g.rows;
   const dim3 grid((unsigned)((p.V + 255) / 256 + 7) / 8 * 8 * q.mgroups);

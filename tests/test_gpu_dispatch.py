@@ -84,3 +84,26 @@ def test_short_logit_rows_are_read_whole_while_they_are_few(B, V, k, one):
 ])
 def test_long_probability_rows_need_many_residuals(B, V, k, one):
     assert (accept_kernels(sx.SPEXIS_INPUT_PROBS, B, V, k) == ["accept_probs_kernel"]) == one
+
+
+def head_kernels(rows, V, d=256):
+    h = torch.zeros((rows, d), dtype=torch.bfloat16, device="cuda")
+    w = torch.zeros(sx.spexis_packed_weight_size(V, d) // 2, dtype=torch.bfloat16, device="cuda")
+    logits = torch.empty((rows, V), device="cuda")
+    stats = torch.empty((rows, sx.spexis_lm_head_tiles(V), 2), device="cuda")
+    got = launched(lambda: sx.spexis_lm_head(h, w, stats, logits=logits))
+    say(f"[head] {rows} @ {V}: {got}")
+    assert len(got) == 1 and (logits == 0).all()
+    return got[0]
+
+
+@pytest.mark.parametrize("rows,V,kernel", [
+    (160, 32000, "lm_head_pair_kernel<5"), (192, 32000, "lm_head_wide_kernel<3"), (320, 32000, "lm_head_wide_kernel<5"),
+    (321, 32000, "lm_head_kernel<false, 6"), (384, 32000, "lm_head_kernel<false, 6"),   # one round, not one and a half
+    (480, 32000, "lm_head_pair_kernel<5"), (512, 32000, "lm_head_pair_kernel<4"), (640, 32000, "lm_head_wide_kernel<5"),
+    (768, 16000, "lm_head_kernel<false, 6"), (832, 20000, "lm_head_wide_kernel<5"),     # one round, not two
+    (352, 65024, "lm_head_pair_kernel<4"), (352, 4096, "lm_head_pair_kernel<4"),
+])
+def test_head_rows_follow_the_rounds_of_workgroups(rows, V, kernel):
+    got = head_kernels(rows, V)
+    assert got.startswith(kernel), got
