@@ -212,6 +212,9 @@ hipError_t launch_projection(const LmParams& p, hipStream_t s);
 // Workgroups launch_projection runs for M rows and N columns (without a K split; at most 8 more
 // are launched to round the column workgroups up to a multiple of 8 per row group).
 int64_t projection_workgroups(int64_t M, int64_t N);
+// Its row groups with a K split and more than 128 rows, and its workgroups of 256 columns with the absent ones.
+int64_t group_rows(int64_t M);
+int64_t launched_workgroups(int64_t N, int64_t groups);
 hipError_t launch_softmax(const float* logits, float* probs, int64_t rows, int V, float c, hipStream_t s);
 hipError_t launch_accept(const AcceptParams& p, hipStream_t s);
 hipError_t launch_gather_columns(const int32_t* qsl, const int32_t* ids, int B, int T, int32_t* cols, hipStream_t s);

@@ -10,6 +10,8 @@
 // without a split the projection writes bf16 (with the residual) itself.  Several layers of one input
 // (the attention layer's q, k, v) run as one layer of their stacked weights whose columns go each to
 // their own output.
+#include <cmath>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -276,22 +278,53 @@ static hipError_t launch_linear_t(const LinearParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Microseconds of linear_kernel's shape 3 and of the projection with its reduce, for more than 128 rows.  Both go
+// by whole rounds of workgroups over the CUs: a CU's time for one of linear_kernel's grows with K alone (two
+// share it, so a round is one for each CU), and for one of the projection's with its part of K and its rows;
+// the fp32 partials are written and read.  Fitted to 700 shapes of 2048 to 8192 x 256 to 28672 at 144 to 2048
+// rows: the kernel taken was within 8% of the quicker one.  The longer K, the more a round and a bit costs: 54.3
+// against 42.5 us at 320 x 4096 x 8192, 56.9 against 39.1 at 160 x 6144 x 8192, but 56.4 against 74.3 at 512 x 3584
+// x 8192 and 29.5 against 32.7 at 320 x 4096 x 4096 (linear_kernel against the projection).
+static double linear_us(int64_t M, int64_t N, int64_t K) {
+  const int64_t wgs = ((N + 63) / 64 + 7) / 8 * 8 * ((M + 63) / 64);
+  return 2 + 3.2 / 1024 * K * ((wgs + 255) / 256);
+}
+static double projection_us(int64_t M, int64_t N, int64_t K) {
+  const int64_t S = linear_split((int)M, (int)N, (int)K), g = group_rows(M);
+  if (S == 1) return INFINITY;   // narrow and without a split: a few CUs do it all
+  const int64_t wgs = launched_workgroups(N, (M + g - 1) / g) * S;
+  return 6 + 0.017 / 160 * g * K / S * ((wgs + 255) / 256) + 8.0 / 5e6 * M * N * S;
+}
+
 // The shape of linear_kernel for a problem, or 0 for the projection kernel (K split over workgroups,
 // then the reduce): 1: 32 rows x 32 columns, 2: 64 x 32, 3: 64 x 64 per workgroup.  The smallest tile
 // whose workgroups fit the 256 CUs at once, and one of 32 rows for up to 32.  Measured (weights from
 // HBM, projection and reduce against linear_kernel): 13.4 against 10.1 us at 1 x 4096 x 4096, 17.8
 // against 11.9 at 64 x 4096 x 4096 (shape 1; shape 2: 15.2), 25.1 against 16.1 at 64 x 6144 x 4096
 // (shape 2; shape 1: 19.8), 36.2 against 21.2 at 128 x 6144 x 4096 (shape 3; shape 2: 25.3), 52.6
-// against 26.9 at 512 x 3584 x 3584 (shape 3).  Where the projection's own tiles fill the chip it reads
-// less per output: 102 against 146 us at 2048 x 4096 x 4096 and 70.5 against 74.7 at 128 x 28672 x 4096
-// (63.0 against 57.8 at 1024 x 4096 x 4096), and a long K (14336: 26.1 against 29.7 us at 16 rows x
-// 4096) is better split over workgroups.
+// against 26.9 at 512 x 3584 x 3584 (shape 3).  The projection is the quicker one
+//   * for a long K and few workgroups, whose waves are one long chain each: 14.1 against 20.2 us at 32 x 1024 x
+//     8192, 11.7 against 14.4 at 1 x 256 x 8192, 17.2 against 21.0 at 64 x 2048 x 8192 (15.1 against 14.2 at 64 x
+//     2048 x 6144); 29.7 against 26.1 at 16 x 4096 x 14336;
+//   * where its own tiles fill the chip: over 32640 columns, without a split, 7.7 against 10.0 us at 1 x 32768 x
+//     256, 84.6 against 93.3 at 32 x 32768 x 8192 (but 12.4 against 9.9 at 33 x 32768 x 256); 101 against 152 us
+//     at 2048 x 4096 x 4096, 73.4 against 75.5 at 128 x 28672 x 4096.  (62.9 against 59.1 at 1024 x 4096 x 4096;
+//     past 1024 workgroups, to about 1400, some sizes would still gain by linear_kernel: 133 against 75 us at
+//     1280 x 4096 x 4096);
+//   * where linear_kernel's rounds are half empty (above; 63.4 against 68.2 us at 128 x 10240 x 8192).
 static int linear_shape(int M, int N, int K) {
   if (K > 8192 || N > 32768) return 0;
   const int64_t tiles = (N + 31) / 32, g64 = (M + 63) / 64;
-  if (M <= 32 || tiles * ((M + 31) / 32) <= 256) return 1;
+  if (M <= 32) {
+    const bool chain = N <= 4096 && (int64_t)K * (M + 64) >= 300000 + 72 * (int64_t)N;
+    return chain || (N > 32640 && (K < 512 || K > 4096)) ? 0 : 1;
+  }
+  if (tiles * ((M + 31) / 32) <= 256) return M <= 64 && N <= 3072 && K > 6144 ? 0 : 1;
   if (tiles * g64 <= 256) return 2;
-  return (tiles + 1) / 2 * g64 <= (M <= 128 ? 512 : 1024) ? 3 : 0;
+  const int64_t wgs = (tiles + 1) / 2 * g64;
+  if (M <= 64) return N > 32640 && K >= 4096 ? 0 : 3;
+  if (M <= 128) return wgs > (K > 6144 ? 256 : 512) ? 0 : 3;
+  return wgs <= 1024 && linear_us(M, N, K) <= projection_us(M, N, K) ? 3 : 0;
 }
 
 hipError_t launch_linear(const LinearParams& p, hipStream_t s) {

@@ -780,7 +780,7 @@ static hipError_t launch_lm_nrt(const LmParams& q, hipStream_t s) {
 static bool wide_columns(int64_t M, int64_t N) { return M > 128 || (N + 255) / 256 >= 256; }
 
 // Workgroups of a launch, with the absent ones that round the column tiles up to the 8 XCDs.
-static int64_t launched_workgroups(int64_t N, int64_t groups) { return ((N + 255) / 256 + 7) / 8 * 8 * groups; }
+int64_t launched_workgroups(int64_t N, int64_t groups) { return ((N + 255) / 256 + 7) / 8 * 8 * groups; }
 
 // More than 128 rows: the kernel and the rows of its groups.  129 to 160 rows are one group of
 // lm_head_pair_kernel, 161 to 320 one of lm_head_wide_kernel with the smallest of three heights that holds
@@ -816,7 +816,7 @@ static_assert((int64_t)kMaxOffsetDim * 320 * 2 < (1ll << 31), "the rows of a gro
 
 // Row groups of lm_head_kernel, which keeps K splits (and their odd step counts): 192 rows (six tiles) when
 // that pads M to at most 5% more rows than groups of 160 (five tiles), else 160.
-static int64_t group_rows(int64_t M) {
+int64_t group_rows(int64_t M) {
   const int64_t p160 = (M + 159) / 160 * 160, p192 = (M + 191) / 192 * 192;
   return p192 * 20 <= p160 * 21 ? 192 : 160;
 }
@@ -824,6 +824,8 @@ static int64_t group_rows(int64_t M) {
 // Few columns, where lm_head_kernel's groups are one workgroup for each CU and the pair kernel's are not two:
 // some CUs then run two of its workgroups and the others wait (100 against 113 us at 352 x 3584 @ 32000, 95
 // against 102 at 768 @ 16000; with two for each CU the pair kernel wins: 118 against 143 us at 480 @ 32000).
+// Not with bf16 outputs, whose many small stores pass under the other workgroup's products: 106 against 83 us
+// at 896 x 2048 @ 10240, 68 against 54 at 512 x 256 @ 18944.
 static bool one_round_of_rows(int64_t M, int64_t N) {
   const RowGroups g = row_groups(M, N);
   if (g.wide || M <= 160 || launched_workgroups(N, (M + g.rows - 1) / g.rows) <= 256) return false;
@@ -862,7 +864,7 @@ hipError_t launch_projection(const LmParams& p, hipStream_t s) {
   if (need <= 1) return launch_lm_nrt<1, 2, 1, 2, 4, 2>(p, s);
   if (need <= 2) return launch_lm_nrt<2, 2, 1, 2, 4, 2>(p, s);
   if (need <= 4) return launch_lm_nrt<4, 2, 1, 2, 4, 1>(p, s);
-  if (p.ksplit > 1 || p.d > kMaxOffsetDim || one_round_of_rows(p.M, p.V))
+  if (p.ksplit > 1 || p.d > kMaxOffsetDim || (!p.y && one_round_of_rows(p.M, p.V)))
     return group_rows(p.M) == 192 ? launch_lm_nrt<6, 2, 1, 2, 4, 1>(p, s) : launch_lm_nrt<5, 2, 1, 2, 4, 1>(p, s);
   const RowGroups g = row_groups(p.M, p.V);
   LmParams q = p;

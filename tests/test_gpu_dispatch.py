@@ -18,7 +18,7 @@ def launched(call) -> list:
     """Names of this library's kernels that call() launches, without their arguments."""
     call()   # the first call loads the kernels
     torch.cuda.synchronize()
-    with profile(activities=[ProfilerActivity.CUDA]) as p:
+    with profile(activities=[ProfilerActivity.CUDA], acc_events=True) as p:
         call()
         torch.cuda.synchronize()
     names = [e.name for e in p.events() if "spexis::" in e.name]
@@ -107,3 +107,25 @@ def head_kernels(rows, V, d=256):
 def test_head_rows_follow_the_rounds_of_workgroups(rows, V, kernel):
     got = head_kernels(rows, V)
     assert got.startswith(kernel), got
+
+
+@pytest.mark.parametrize("rows,n_out,n_in,kernel", [
+    (1, 256, 4096, "linear_kernel<1, 1, 8"), (1, 256, 8192, None), (32, 1024, 8192, None), (32, 5120, 8192, "linear_kernel<1, 1, 8"),
+    (64, 2048, 6144, "linear_kernel<1, 1, 8"), (64, 2048, 8192, None), (1, 32768, 256, None), (64, 32768, 1024, "linear_kernel<2, 2, 4"),
+    (128, 6144, 8192, "linear_kernel<2, 2, 4"), (128, 10240, 8192, None), (160, 6144, 8192, None),
+    (320, 4096, 4096, "linear_kernel<2, 2, 4"), (320, 4096, 8192, None), (512, 3584, 8192, "linear_kernel<2, 2, 4"),
+    (2048, 2048, 8192, None),
+])
+def test_adapter_layers_take_the_quicker_kernel(rows, n_out, n_in, kernel):
+    # None: the projection, its K split over workgroups, and the reduce
+    x = torch.zeros((rows, n_in), dtype=torch.bfloat16, device="cuda")
+    w = torch.zeros(sx.spexis_packed_weight_size(n_out, n_in) // 2, dtype=torch.bfloat16, device="cuda")
+    y = torch.empty((rows, n_out), dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(max(sx.spexis_linear_workspace_size(rows, n_out, n_in), 1), dtype=torch.uint8, device="cuda")
+    got = launched(lambda: sx.spexis_linear(x, w, y, workspace=ws))
+    say(f"[linear] {rows} x {n_out} x {n_in}: {got}")
+    assert (y == 0).all()
+    if kernel:
+        assert len(got) == 1 and got[0].startswith(kernel)
+    else:
+        assert got[0].startswith("lm_head") and got[1:] in ([], ["linear_reduce_kernel"])
