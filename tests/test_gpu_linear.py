@@ -98,7 +98,7 @@ def test_linear_split_matches_oracle(rows, widths, n_in):
 
 def test_linear_split_equals_one_stacked_layer():
     # the same stacked weight through spexis_linear: the outputs are its column blocks, bit for bit
-    # whenever both take the same K split (they do here: one problem size)
+    # (one problem size: both take the same kernel, which adds its parts of K in the same order)
     rows, widths, n_in = 64, [4096, 1024, 1024], 4096
     x, _ = bf16_pair((rows, n_in), 21, 1.0)
     w, _ = bf16_pair((sum(widths), n_in), 22, 0.03)
@@ -115,7 +115,8 @@ def test_linear_split_equals_one_stacked_layer():
 
 def test_linear_output_may_alias_residual():
     check(48, 256, 512, True, 14, alias=True)
-    check(64, 4096, 1024, True, 15, alias=True)   # K split: the reduce pass reads the residual
+    check(64, 4096, 1024, True, 15, alias=True)   # one launch: the thread that stores an output reads its residual
+    check(40, 256, 8448, True, 16, alias=True)    # K split over workgroups: the reduce pass reads it
 
 
 def test_linear_rejects_bad_arguments():
@@ -133,7 +134,15 @@ def test_linear_rejects_bad_arguments():
     y = torch.empty((64, 4096), dtype=torch.bfloat16, device="cuda")
     assert sx.spexis_linear_workspace_size(64, 4096, 1024) > 0
     with pytest.raises(sx.SpexisError) as e:
-        sx.spexis_linear(x, w, y)
+        sx.spexis_linear(x, w, y)   # (this problem's one launch would not use it)
+    assert e.value.code == sx.SPEXIS_ERR_WORKSPACE_TOO_SMALL
+    x = torch.zeros((64, 8448), dtype=torch.bfloat16, device="cuda")
+    w = sx.spexis_pack_weight(torch.zeros((256, 8448), dtype=torch.bfloat16, device="cuda"))
+    y = torch.empty((64, 256), dtype=torch.bfloat16, device="cuda")
+    need = sx.spexis_linear_workspace_size(64, 256, 8448)
+    ws = torch.empty(need - 1, dtype=torch.uint8, device="cuda")
+    with pytest.raises(sx.SpexisError) as e:
+        sx.spexis_linear(x, w, y, workspace=ws)
     assert e.value.code == sx.SPEXIS_ERR_WORKSPACE_TOO_SMALL
 
 
@@ -175,6 +184,28 @@ def test_pack_weight_layout(N, K):
 ])
 def test_linear_tile_edges(rows, n_out, n_in, res):
     check(rows, n_out, n_in, res, rows * 7 + n_out)
+
+
+# K past 8192: the projection with K split over workgroups (here by 4, for at most 256 workgroups and partials of no
+# more than the weight's traffic), then the reduce
+@pytest.mark.parametrize("rows,n_out,res", [
+    (64, 200, False), (33, 130, True),     # two row tiles
+    (100, 260, True), (128, 4096, False),  # four
+    (192, 300, True), (176, 260, False),   # a group of 192 rows
+    (500, 300, True),                      # three of them
+])
+def test_linear_k_split(rows, n_out, res):
+    sample = None if rows < 200 and n_out < 1000 else [0, 31, rows // 2, rows - 1]
+    assert sx.spexis_linear_workspace_size(rows, n_out, 8448) > 0
+    check(rows, n_out, 8448, res, rows * 3 + n_out, sample=sample)
+
+
+@pytest.mark.parametrize("rows,widths,n_in", [
+    (5, [12, 100, 4], 8448), (64, [256, 64, 64], 8448), (190, [128, 4, 60, 8], 8448),   # K split: partials routed
+    (3, [32768, 64, 4], 256), (140, [32704, 100], 256),                                 # no split: products routed
+])
+def test_linear_split_past_the_one_launch_kernel(rows, widths, n_in):
+    test_linear_split_matches_oracle(rows, widths, n_in)
 
 
 @pytest.mark.parametrize("n_out", [40, 42])
