@@ -309,17 +309,10 @@ __device__ void sub_maxima(const AcceptParams& p, const RowCtx& r, bool residual
   }
 }
 
-// The scale of the sampled row, M = the largest probability of target row a (with logits
-// 2^0 * (1/Z), from its statistics), and whether a row the sampling reads holds a NaN, an
-// infinity or a negative value (with logits: a row whose statistics are not finite).  One
-// full wave; every consumer gets the same values.
-__device__ __forceinline__ void sampled_scale(const AcceptParams& p, const RowCtx& r, int b, bool residual, int lane,
-                                              float& M, int& bad) {
-  if (r.logits) {
-    M = r.Rp;
-    bad = !(r.Rp > 0.f) || isinf(r.Rp) || (residual && (!(r.Rq > 0.f) || isinf(r.Rq)));
-    return;
-  }
+// Probability inputs: the scale of the sampled row, M = the largest probability of target row a, and
+// whether a row the sampling reads holds a NaN, an infinity or a negative value, from sub_maxima's
+// partials.  One full wave; every consumer gets the same values.
+__device__ __forceinline__ void sampled_scale(const AcceptParams& p, int b, int lane, float& M, int& bad) {
   M = 0.f;
   bad = 0;
   for (int x = lane; x < p.nsub; x += kWave) {
@@ -367,20 +360,19 @@ __device__ void sub_sums(const AcceptParams& p, const RowCtx& r, bool residual, 
   }
 }
 
-// The sampled row(s) of sequence b at position a over sub-chunk `sub`: entries, statistics,
+// Probability inputs: the sampled row(s) of sequence b at position a over sub-chunk `sub`: entries,
 // scale, then the fixed-point sums (a bad or empty row writes none; the search reports it).
 __device__ void sample_sums(const AcceptParams& p, int b, const Geom& g, int a, bool residual, int sub, int wave,
                             int lane) {
   const bool vec = (p.V & 3) == 0;
-  const float fill = p.kind == 1 ? -INFINITY : 0.f;
-  // the entries first: their loads overlap the reductions of the row statistics and maxima
+  // the entries first: their loads overlap the reduction of the maxima
   float pv[kPerLane], qv[kPerLane];
   // non-temporal: the search reads back one sub-chunk of these rows at most (measured: the
   // acceptance of 512 sequences of 152064-entry rows 6 us faster, a whole verification step
   // about 2 us, and no slower at 64 sequences of 128256)
-  load_sub<true>(p.target + (int64_t)(g.t0 + a) * p.V, sub, wave, p.V, vec, fill, lane, pv);
+  load_sub<true>(p.target + (int64_t)(g.t0 + a) * p.V, sub, wave, p.V, vec, 0.f, lane, pv);
   if (residual) {
-    load_sub<true>(p.draft + (int64_t)(g.d0 + a) * p.V, sub, wave, p.V, vec, fill, lane, qv);
+    load_sub<true>(p.draft + (int64_t)(g.d0 + a) * p.V, sub, wave, p.V, vec, 0.f, lane, qv);
   } else {
 #pragma unroll
     for (int e = 0; e < kPerLane; ++e) qv[e] = 0.f;
@@ -388,7 +380,7 @@ __device__ void sample_sums(const AcceptParams& p, int b, const Geom& g, int a, 
   const RowCtx r = row_ctx(p, b, g, a, residual, lane);
   float M;
   int bad;
-  sampled_scale(p, r, b, residual, lane, M, bad);
+  sampled_scale(p, b, lane, M, bad);
   if (sub == 0 && threadIdx.x == 0) {
     // the search's record: geometry, position and mode, bad flag and scale, row statistics
     u32x4* rec = reinterpret_cast<u32x4*>(p.srec) + 3 * (int64_t)b;
@@ -473,18 +465,12 @@ __device__ __forceinline__ void store_geom_state(const AcceptParams& p, int b, c
   *reinterpret_cast<u32x4*>(p.geo + 4 * (int64_t)b) = u32x4{(uint32_t)g.t0, (uint32_t)g.d0, (uint32_t)g.k, (uint32_t)state};
 }
 
-// Sequence li of round r's list: all sequences in round 0 (their stored record; with no drafts
-// at all there are no ids to check, and no pass before writes one), the ones still accepting
-// after.
+// Sequence li of round r's list: all sequences in round 0 (the record the statistics pass stored), the
+// ones still accepting after.
 __device__ __forceinline__ void round_seq(const AcceptParams& p, int r, int li, int& b, Geom& g) {
   if (r == 0) {
     b = li;
-    if (p.max_k == 0) {
-      int n;
-      g = seq_geom(p, b, n);
-    } else {
-      g = load_geom(p, b);
-    }
+    g = load_geom(p, b);
     return;
   }
   const u32x4 e = *reinterpret_cast<const u32x4*>(p.lists + ((int64_t)(r - 1) * p.B + li) * 4);
@@ -1135,8 +1121,8 @@ __device__ __forceinline__ void sample_held(const AcceptParams& p, const RowCtx&
 }
 
 // load4 with the row's form known at compile time: kVec for V a multiple of 4, whose four entries are
-// all inside or all past the row (one predicate a load instead of five keeps the kernels below free of
-// spilled registers).
+// all inside or all past the row (one predicate a load instead of five, whose masks take scalar registers: for
+// other lengths accept_short_kernel spills over a hundred of them to vector lanes).
 template <bool kVec>
 __device__ __forceinline__ f32x4 load4_of(const float* row, int e, int V, float fill) {
   if (!kVec) return load4(row, e, V, false, fill);
@@ -1157,7 +1143,8 @@ __device__ __forceinline__ void hold_row(const float* row, int V, float fill, fl
 // Probability rows of up to 4 TH F4 entries, one workgroup per sequence: the tests need two gathers each
 // and a lane each, then the sampled position's rows are read once, into registers, for their checks, their
 // scale, the sums and the token.  Four launches (tests, maxima, sums, search) read them twice: 29.3 against
-// 20.9 us at 128 sequences of 32000 entries, 4 drafts each.
+// 20.9 us at 128 sequences of 32000 entries, 4 drafts each.  With 32 entries of each row a thread (F4 = 8) the two
+// rows and the 64-bit sums exceed the 128 registers that 16 waves leave a thread; about 40 spill to scratch.
 template <int TH, int F4, bool kVec>
 __global__ __launch_bounds__(TH) void accept_probs_kernel(AcceptParams p) {
   constexpr int NW = TH / kWave, NE = 4 * F4;

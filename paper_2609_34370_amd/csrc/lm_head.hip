@@ -443,6 +443,7 @@ void lm_head_wide_kernel(LmParams p) {
   // 0 and 1.
   constexpr int kHStage = kRows * 8, kWStage = kCols / 32 * 256;
   __shared__ u32x4 sm[2 * kHStage + 2 * kWStage];
+  static_assert(2 * kHStage >= WR * WC * 32 * 36 / 4, "the epilogue transposes a tile per wave through the h stages");
   // Copies go from memory straight into a stage (buffer loads to LDS, 1 KB per wave and
   // instruction, lane l's 16 bytes at slot 64 u + l): no staging registers, which leaves room
   // for two sets of operand fragments.  Buffer resources span the group's rows of h and the
@@ -577,7 +578,7 @@ void lm_head_wide_kernel(LmParams p) {
   }
   k_step(Stage0{}, std::true_type{}, std::false_type{}, j);
   k_step(Stage1{}, std::false_type{}, std::false_type{}, j + 1);
-  __syncthreads();   // the epilogue's transposes reuse h stage 0
+  __syncthreads();   // the epilogue's transposes reuse the h stages
 
   // ---- epilogue (the gather columns first, as above)
   int gcol[RT];
@@ -589,7 +590,7 @@ void lm_head_wide_kernel(LmParams p) {
   store_epilogue<RT, CT, WR, WC>(acc, p.logits, reinterpret_cast<uint16_t*>(p.y),
                                  reinterpret_cast<const uint16_t*>(p.res), p.V, m0, n0, rows, wr, wc, lane);
   if (!p.stats) return;
-  __shared__ float sm_m[WC][kRows], sm_z[WC][kRows];   // the transposes: the (now free) h stage 0
+  __shared__ float sm_m[WC][kRows], sm_z[WC][kRows];   // the transposes: the (now free) h stages
   row_stats_epilogue<RT, CT, WR, WC>(p.stats, p.gout, p.c, p.V, p.ntiles, acc, gcol, nt, m0, n0, rows, wr, wc, lane, reinterpret_cast<float*>(&sm[0]),
                                      sm_m, sm_z);
 }
