@@ -376,7 +376,8 @@ size_t spexis_packed_weight_size(int32_t rows, int32_t cols);
  *   residual  [rows][out_features] bf16 or NULL;  y: [rows][out_features] bf16 output (may not
  *             alias x or weight; may alias residual)
  *   workspace >= spexis_linear_workspace_size(rows, out_features, in_features) bytes (0 when
- *             the problem fills the chip without splitting K; then it may be NULL)
+ *             the projection fills the chip without splitting K; then it may be NULL).  A problem
+ *             that one launch computes leaves it untouched, but it is asked for all the same
  * Supported: in_features % 256 == 0.  Errors: INVALID_ARGUMENT, UNSUPPORTED,
  * WORKSPACE_TOO_SMALL, HIP.
  */
@@ -393,15 +394,16 @@ size_t spexis_linear_workspace_size(int32_t rows, int32_t out_features, int32_t 
  * order (spexis_pack_weight of the stacked rows), and output i receives its columns of x W^T:
  *   y_i[r][o] = bf16( sum_j x[r][j] * W[c_i + o][j] ),   c_i = out_features[0] + ... + [i-1]
  * with fp32 accumulation (the order over j is the library's) and one round to nearest even; no
- * residual.  One launch computes and routes all columns (large layers: a projection, and a launch that
- * adds the K-split partials and routes each layer's columns): at few rows, where each launch is latency-bound, fewer launches than one
- * spexis_linear per layer.
+ * residual.  One launch computes and routes all columns (large layers: a projection, and a launch
+ * that adds the K-split partials and routes each layer's columns): at few rows, where each launch is
+ * latency-bound, fewer launches than one spexis_linear per layer.
  *   x            [rows][in_features] bf16
  *   num_outputs  1 .. 4;  out_features: host [num_outputs], each > 0 and a multiple of 4
  *   outputs      host [num_outputs] of device pointers: output i is [rows][out_features[i]]
  *                bf16 (may not alias x, weight or one another)
  *   workspace    >= spexis_linear_split_workspace_size(rows, sum of out_features, in_features)
- *                bytes (the fp32 products pass through it: never 0 when rows > 0)
+ *                bytes, never 0 when rows > 0 (the fp32 products of large layers pass through it; one
+ *                launch leaves it untouched, but it is asked for all the same)
  * Supported: in_features % 256 == 0.  Errors: INVALID_ARGUMENT (bad sizes or count, NULL
  * pointers), UNSUPPORTED (widths, in_features, size), WORKSPACE_TOO_SMALL, HIP.
  */
