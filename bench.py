@@ -743,11 +743,11 @@ def bench_draft(args):
 
 
 COPY_KERNEL = "copyBuffer"
-# per call: (kernel-name fragments of its launches, the launch that runs exactly once per call,
+# per call: (kernel-name fragments of its launches, the launches of which each call makes exactly one,
 # the sources its kernels are built from)
 TRAFFIC_CALLS = {
-    "verify_attention": (("verify_attn_kernel", "attn_merge_kernel"), "verify_attn_kernel", ("attention.hip",)),
-    "accept": (("accept_",), "accept_search_kernel", ("accept.hip",)),
+    "verify_attention": (("verify_attn_kernel", "attn_merge_"), ("verify_attn_kernel",), ("attention.hip",)),
+    "accept": (("accept_",), ("accept_search_kernel", "accept_probs_kernel", "accept_short_kernel"), ("accept.hip",)),
 }
 
 
@@ -778,10 +778,10 @@ def ingest_traffic(fetch_csv: str, write_csv: str, workload: int, copy_bytes: in
         readings[name] = (k, float(np.median(probe)))
     prof = os.path.join(ROOT, "profiles", "traffic.json")
     data = json.load(open(prof)) if os.path.exists(prof) else {}
-    for call, (frags, anchor, sources) in TRAFFIC_CALLS.items():
+    for call, (frags, anchors, sources) in TRAFFIC_CALLS.items():
         result = {}
         for name, (k, probe) in readings.items():
-            calls = sum(len(vals) for n, vals in k.items() if anchor in n)
+            calls = sum(len(vals) for n, vals in k.items() if any(a in n for a in anchors))
             if calls == 0:
                 break
             raw = sum(sum(vals) for n, vals in k.items() if any(f in n for f in frags)) / calls

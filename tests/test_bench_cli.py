@@ -89,6 +89,32 @@ def test_traffic_is_scaled_by_the_copy_reading(tmp_path, monkeypatch):
     assert ac["counters"]["FETCH_SIZE"]["calls"] == 2
 
 
+def test_traffic_counts_every_kernel_a_call_may_launch(tmp_path, monkeypatch):
+    # the merge that spreads an item over a workgroup, and acceptance in one launch (a run of both forms:
+    # short logit rows, probabilities, and the launches that end in the search)
+    bench = load_bench()
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    monkeypatch.setattr(bench, "_kernel_digest", lambda sources=(): "digest")
+    (tmp_path / "profiles").mkdir()
+    kib = 1.0 / 1024.0
+    rows = [("__amd_rocclr_copyBuffer", 1e6 * kib)] * 3 + [
+        ("void spexis::verify_attn_kernel<128, 16, 1>(spexis::AttnParams)", 50e6 * kib),
+        ("void spexis::attn_merge_wide_kernel<128>(spexis::AttnParams, int)", 7e6 * kib),
+        ("void spexis::accept_short_kernel<true>(spexis::AcceptParams)", 3e6 * kib),
+        ("void spexis::accept_probs_kernel<1024, 8, true>(spexis::AcceptParams)", 5e6 * kib),
+        ("spexis::accept_given_kernel(spexis::AcceptParams)", 1e6 * kib),
+        ("spexis::accept_stream_kernel(spexis::AcceptParams, int)", 8e6 * kib),
+        ("spexis::accept_search_kernel(spexis::AcceptParams)", 1e6 * kib)]
+    for name, counter in (("f.csv", "FETCH_SIZE"), ("w.csv", "WRITE_SIZE")):
+        write_counters(tmp_path / name, counter, rows)
+    bench.ingest_traffic(str(tmp_path / "f.csv"), str(tmp_path / "w.csv"), 2, 10 ** 6)
+    import json
+    data = json.load(open(tmp_path / "profiles" / "traffic.json"))
+    np.testing.assert_allclose(data["workload2:verify_attention"]["bytes_per_launch"], 2 * 57e6, rtol=1e-9)
+    assert data["workload2:accept"]["counters"]["FETCH_SIZE"]["calls"] == 3
+    np.testing.assert_allclose(data["workload2:accept"]["bytes_per_launch"], 2 * 18e6 / 3, rtol=1e-6)
+
+
 def test_accept_bytes_follow_the_rows_a_sequence_reaches():
     # logits mode: both normalisers of rows 0..a (target and draft, the draft only up to k-1),
     # then the sampled rows again: residual (target + draft row a) or bonus (target row k)
